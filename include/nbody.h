@@ -198,7 +198,15 @@ typedef struct nbody_exclusions {
  *             64-record chunks as the workgroup has waves; otherwise 1): more
  *             parts fill the chip's last round of tiles better and leave more
  *             slot partials for the reduction to read.  The requested value is
- *             rounded down to the nearest allowed one. */
+ *             rounded down to the nearest allowed one.
+ *             3 = fine pair tiles, in one shape (block 256, i_per_lane 2, j_tile
+ *             512): each unordered pair of a whole system once, in quarter sweeps
+ *             shared out equally over the workgroups; the rule's choice for
+ *             FP32_KAHAN and FP32_FP64ACC from 2,048 to 32,767 particles (forces
+ *             and leapfrog of every law, gravity's backward, LJC(linear)'s from
+ *             2,560 to 16,383 atoms, the shared Hermite steps), and for the
+ *             forces and leapfrog of every law in FP64 from 2,048 to 262,144
+ *             particles. */
 typedef struct nbody_config {
     int32_t block;
     int32_t i_per_lane;
@@ -446,8 +454,9 @@ int nbody_forces_jerk(const double *pos, const double *vel, const double *mass, 
  *  device.  law as nbody_forces_jerk.  dt > 0 finite, nsteps >= 0.  The
  *  update is FP64; the pair arithmetic follows law->precision.  Each step
  *  evaluates every particle as nbody_forces_jerk would for the whole system
- *  where its configuration (NBODY_API_JERK) selects the symmetric tiles,
- *  and otherwise with the NBODY_API_HERMITE configuration.
+ *  where its configuration (NBODY_API_JERK) selects the symmetric tiles, over
+ *  the fine tiles from 2,048 to 32,767 particles where neither configuration
+ *  is forced or tuned, and otherwise with the NBODY_API_HERMITE configuration.
  * Workspace: nbody_workspace_bytes(NBODY_API_HERMITE, n, 1, law). */
 int hermite_step(double *pos, double *vel, double *acc, double *jerk, const double *mass,
                  int64_t n, const nbody_law *law, double dt, int32_t nsteps, void *ws,

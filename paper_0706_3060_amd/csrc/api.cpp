@@ -23,6 +23,7 @@
 #include "adjoint.h"
 #include "jerk.h"
 #include "kernels.h"
+#include "fine.h"
 #include "noalloc.h"
 #include "probe.h"
 
@@ -144,6 +145,57 @@ size_t symadj_ljc_partial_bytes(int64_t n)
     const int64_t np = round_up(std::max<int64_t>(n, 1), kBSymRecords);
     return (size_t)(np / kBSymRecords) * (size_t)np * 8 * sizeof(float);
 }
+
+// The fine pair tiles (fine.inl, j_stage 3): every unordered pair of a whole system once, in work
+// units small enough to fill the chip between the smallest systems and the sizes of the coarser
+// tiles; and, for FP64 pair arithmetic, which has no coarser tiles, up to kFineMaxN (4 GiB of slots).
+// The rule's lines, per call against the one-sided kernels (us, FP32 + Kahan unless said): at 2,050
+// particles 18-22 against 21-26 for gravity, LJC(linear), the jerk and gravity's adjoint, FP64 22
+// against 23; at 8,192 gravity 29 against 39, LJC(linear) with energies 38 against 52, the jerk 48
+// against 64, gravity's adjoint 37 against 60, FP64 gravity 49 against 86; at 50,001 FP64 gravity 1,158
+// against 1,870.  LJC(linear)'s adjoint, six sums a particle: 28 against 25 at 2,050, 28 against 32 at
+// 3,000, 64 against 91 at 8,192; from 16,384 atoms its 256-record tiles do as well.  From 32,768 FP32
+// particles the coarser tiles do as well (within 3 % at 50,001) with fewer slots.
+constexpr int kFineStage = 3;
+constexpr int64_t kFineMinN = 2048;
+constexpr int64_t kFineAdjLjcMinN = 2560;
+bool sym_eligible(int api, int law, int prec);
+int fine_op_of(int api, int law)
+{
+    if (api == NBODY_API_JERK) return FINE_JERK;
+    if (api == NBODY_API_BACKWARD) return law == NBODY_LAW_GRAVITY ? FINE_HVP : FINE_LJC_ADJ;
+    return FINE_FORCE;
+}
+// the largest system of the fine tiles, 0 where they do not apply
+int64_t fine_max_n(int api, int law, int prec)
+{
+    if (api != NBODY_API_FORCES && api != NBODY_API_LEAPFROG && api != NBODY_API_BACKWARD && api != NBODY_API_JERK)
+        return 0;
+    if (!fine_supported(fine_op_of(api, law), law, prec)) return 0;
+    return is_f32(prec) ? kSymMinN : kFineMaxN;
+}
+int fine_chunks(int64_t n) { return (int)((std::max<int64_t>(n, 1) + 63) / 64); }
+int fine_blocks(int64_t n) { return (fine_chunks(n) + kFineChunks - 1) / kFineChunks; }
+int64_t fine_npad(int64_t n) { return (int64_t)fine_blocks(n) * kFineRows; }
+// most workgroups a launch over n particles has: four quarters of a sweep each at least
+int fine_wgs_bound(int64_t n)
+{
+    return std::min(kFineMaxWgs, (fine_begin(fine_blocks(n), fine_chunks(n)) + 3) / 4);
+}
+// slot buffers: the blocks' j sums, the workgroups' i sums and their carries, one after another
+struct FineSlots {
+    size_t i_off, c_off, total;
+};
+FineSlots fine_slots(int64_t n, int wgs, int op, int prec)
+{
+    const size_t row = (size_t)fine_cols(op) * (is_f32(prec) ? sizeof(float) : sizeof(double));
+    FineSlots f;
+    f.i_off = align256((size_t)fine_blocks(n) * fine_npad(n) * row);
+    f.c_off = f.i_off + align256((size_t)(wgs + fine_blocks(n)) * kFineRows * row);
+    f.total = f.c_off + align256((size_t)wgs * 64 * row);
+    return f;
+}
+size_t fine_partial_bytes(int64_t n, int op, int prec) { return fine_slots(n, fine_wgs_bound(n), op, prec).total; }
 
 bool sym_eligible(int api, int law, int prec)
 {
@@ -287,6 +339,16 @@ Cfg sanitize(Cfg c, int api, int law, int prec, int64_t npad)
             return c;
         }
         c.j_stage = 1;                                  // other laws, precisions, entry points, sizes
+    }
+    if (c.j_stage == kFineStage) {
+        if (npad <= fine_max_n(api, law, prec)) {
+            c.block = kFineWaves * 64;                    // the fine tiles' one shape
+            c.ipl = kFineIch;
+            c.j_tile = kFineRows;
+            c.j_split = 1;
+            return c;
+        }
+        c.j_stage = is_f32(prec) ? 1 : 0;               // elsewhere the precision's one-sided staging
     }
     c.j_stage = std::max(0, std::min(c.j_stage, 1));
     // the one-sided, batched, adjoint and jerk kernels are built for up to 256 threads
@@ -442,6 +504,12 @@ Cfg heuristic(int api, int law, int prec, int64_t n, int64_t nj, int64_t S, bool
         return sanitize(c, api, law, prec, round_up(n, 64));
     }
     const int64_t npad = round_up(std::max<int64_t>(std::max(n, nj), 1), 64);
+    if (allow_sym && n == nj && n >= kFineMinN && npad <= fine_max_n(api, law, prec) &&
+        !(api == NBODY_API_BACKWARD && law == NBODY_LAW_LJC_LINEAR && (n < kFineAdjLjcMinN || n >= kSymAdjLjcMinN)) &&
+        api != NBODY_API_JERK) {
+        c.j_stage = kFineStage;
+        return sanitize(c, api, law, prec, npad);
+    }
     const int smax = max_split_rows(n, nj);
     if (api == NBODY_API_BATCHED || api == NBODY_API_BACKWARD_BATCHED) {
         c.ipl = 1;
@@ -570,9 +638,11 @@ void tune_cache_store()
 }
 
 // The configuration for n output rows in S systems; nj j records (0: nj = n).
-Cfg choose(int api, const nbody_law *law, int64_t n, int64_t S, bool pot, int64_t nj = 0)
+// ruled (or null): whether it is the rule's, neither forced nor tuned.
+Cfg choose(int api, const nbody_law *law, int64_t n, int64_t S, bool pot, int64_t nj = 0, bool *ruled = nullptr)
 {
     tune_cache_load_once();
+    if (ruled) *ruled = false;
     if (nj <= 0) nj = n;
     const int64_t npad = round_up(std::max<int64_t>(std::max(n, nj), 1), 64);
     std::lock_guard<std::mutex> lk(g_mu);
@@ -585,9 +655,10 @@ Cfg choose(int api, const nbody_law *law, int64_t n, int64_t S, bool pot, int64_
                                   law->kind, law->precision, pot ? 1 : 0, size_bucket(n), sb));
     // (the jerk's symmetric tiles evaluate whole systems: not a shape for the block steps, which
     // a shared Hermite step takes from the jerk's own configuration)
-    if (it != g_tuned.end() && api == NBODY_API_HERMITE && it->second.first.j_stage == kSymStage)
+    if (it != g_tuned.end() && api == NBODY_API_HERMITE && it->second.first.j_stage >= kSymStage)
         it = g_tuned.end();
     if (it != g_tuned.end()) return sanitize(it->second.first, api, law->kind, law->precision, npad);
+    if (ruled) *ruled = true;
     return heuristic(api, law->kind, law->precision, n, nj, S, pot);
 }
 
@@ -595,7 +666,7 @@ Cfg choose(int api, const nbody_law *law, int64_t n, int64_t S, bool pot, int64_
 // (which evaluate whole systems only: not row subsets or exclusion lists)
 Cfg one_sided(const Cfg &c, int api, const nbody_law *law, int64_t n, int64_t nj, bool pot)
 {
-    if (c.j_stage != kSymStage) return c;
+    if (c.j_stage < kSymStage) return c;
     return heuristic(api, law->kind, law->precision, n, nj, 1, pot, false);
 }
 
@@ -645,9 +716,13 @@ FwdWs fwd_layout(int api, const nbody_law *law, int64_t n)
     const bool sym = sym_eligible(api, law->kind, law->precision) && n <= kSymMaxN;
     // the symmetric tiles pad the records to whole blocks and keep one FP32 partial per
     // row and block; the one-sided split keeps [split][rows][4] FP64 partials
-    const int64_t nrec = sym ? sym_npad(n, 32) : npad;
+    int64_t nrec = sym ? sym_npad(n, 32) : npad;
     size_t part = (size_t)max_split(npad) * (size_t)npad * 4 * sizeof(double);
     if (sym) part = std::max(part, sym_max_partial_bytes(n));
+    if (npad <= fine_max_n(api, law->kind, law->precision)) {
+        nrec = std::max(nrec, fine_npad(n));
+        part = std::max(part, fine_partial_bytes(n, FINE_FORCE, law->precision));
+    }
     size_t off = 0;
     w.rec_off = off;
     off = align256(off + (size_t)nrec * rec_bytes(law->kind, law->precision));
@@ -680,6 +755,10 @@ AdjWs adj_layout(const nbody_law *law, int64_t n)
     size_t part = (size_t)max_split(npad) * (size_t)npad * 8 * sizeof(double);
     if (sym) part = std::max(part, sym_max_partial_bytes(n));
     if (ljs) part = std::max(part, symadj_ljc_partial_bytes(n));
+    if (npad <= fine_max_n(NBODY_API_BACKWARD, law->kind, law->precision)) {
+        nrec = std::max(nrec, fine_npad(n));
+        part = std::max(part, fine_partial_bytes(n, fine_op_of(NBODY_API_BACKWARD, law->kind), law->precision));
+    }
     size_t off = 0;
     w.rec_off = off;
     off = align256(off + (size_t)nrec * adj_rec_bytes(law->kind, law->precision));
@@ -709,9 +788,13 @@ JerkWs jerk_layout(int api, const nbody_law *law, int64_t n)
     // the symmetric tiles' records (padded to whole blocks) and slot partials, for the sizes
     // they take
     const bool sym = symjerk_ok(law->kind, law->precision) && n <= kSymJerkMaxN;
-    const int64_t nrec = sym ? std::max(npad, symjerk_npad(n)) : npad;
+    int64_t nrec = sym ? std::max(npad, symjerk_npad(n)) : npad;
     size_t part = (size_t)max_split(npad) * (size_t)npad * 8 * sizeof(double);
     if (sym) part = std::max(part, symjerk_partial_bytes(n, symjerk_max_split(n)));
+    if (npad <= fine_max_n(NBODY_API_JERK, law->kind, law->precision)) {
+        nrec = std::max(nrec, fine_npad(n));
+        part = std::max(part, fine_partial_bytes(n, FINE_JERK, law->precision));
+    }
     size_t off = 0;
     w.rec_off = off;
     off = align256(off + (size_t)nrec * 8 * t);
@@ -896,18 +979,76 @@ Epilogue make_epi(const nbody_law *law, double *out_force, double *out_pot)
     return e;
 }
 
+// How the quarter sweeps of n particles are shared out: `per` quarters to each workgroup, m
+// workgroups per CU.  A CU's four SIMDs each run one wave of every workgroup on it, so the launch
+// takes about m * per quarters' time, over the rate a SIMD reaches with m waves to switch between.
+int fine_per(int64_t n)
+{
+    const int total = fine_begin(fine_blocks(n), fine_chunks(n));
+    constexpr double rate[] = {0.0, 0.60, 0.85, 0.96, 1.0};
+    int best = 4;
+    double cost = 1e300;
+    for (int m = 1; m <= 4; ++m) {
+        const int wgs = std::max(1, std::min(kFineMaxWgs, m * device_cus()));
+        const int per = std::max(4, (total + wgs - 1) / wgs);
+        const double t = m * per / rate[m];
+        if (t < cost) {
+            cost = t;
+            best = per;
+        }
+    }
+    return best;
+}
+
+// A fine launch over the records and slot buffers of a workspace; `have` bytes of slots
+FineLaunch make_fine(int op, const nbody_law *law, int64_t n, bool pot, void *rec, void *slots)
+{
+    FineLaunch a{};
+    a.op = op;
+    a.law = law->kind;
+    a.prec = law->precision;
+    a.pot = pot ? 1 : 0;
+    a.n = n;
+    a.nch = fine_chunks(n);
+    a.nb = fine_blocks(n);
+    a.per = fine_per(n);
+    a.nwg = (fine_begin(a.nb, a.nch) + a.per - 1) / a.per;
+    a.eps2 = law->kind == NBODY_LAW_GRAVITY ? law->softening * law->softening : 0.0;
+    for (int c = 0; c < 4; ++c) a.zeta[c] = law->kind == NBODY_LAW_LJC_SIGMOIDAL ? law->zeta[c] : 0.0;
+    const FineSlots f = fine_slots(n, a.nwg, op, law->precision);
+    a.rec = rec;
+    a.jslot = slots;
+    a.islot = (char *)slots + f.i_off;
+    a.carry = (char *)slots + f.c_off;
+    a.G = law->G;
+    a.qscale = qscale_of(law);
+    return a;
+}
+
+int run_fine(const FineLaunch &a, hipStream_t s, bool timed = true)
+{
+    Timer t(s, timed);
+    hipError_t e = launch_fine(a, s);
+    t.stop();
+    if (e != hipSuccess) return hip_fail(e, "fine pair tiles");
+    e = launch_fine_reduce(a, s);
+    if (e != hipSuccess) return hip_fail(e, "fine tiles' slot reduction");
+    return NBODY_OK;
+}
+
 // pack + all-pairs (+ split reduction) for one system already validated
 int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const double *params,
                 int64_t n, const int64_t *rows, int64_t nrows, const Epilogue &epi, bool pot,
                 void *ws, const FwdWs &lay, hipStream_t s, PackLaunch *pk_in,
                 const ExclArgs &excl = ExclArgs{}, bool timed = true, int64_t share = 0,
-                int64_t n_shares = 1)
+                int64_t n_shares = 1, bool packed = false, const FineNext &next = FineNext{})
 {
     // the symmetric tiles (j_stage 2) evaluate whole systems; sanitize admits the
     // configuration only for FP32_KAHAN / FP32_FP64ACC forward laws and gravity's backward
     const bool sym = c.j_stage == kSymStage && rows == nullptr && nrows == n && excl.off == nullptr;
     const int blk = sym ? c.j_tile / 64 : 0;
-    const int64_t npad = sym ? sym_npad(n, blk) : round_up(n, 64);
+    const bool fine = c.j_stage == kFineStage && rows == nullptr && nrows == n && excl.off == nullptr;
+    const int64_t npad = sym ? sym_npad(n, blk) : (fine ? fine_npad(n) : round_up(n, 64));
     char *base = (char *)ws;
     PackLaunch pk{};
     if (pk_in) pk = *pk_in;
@@ -919,9 +1060,17 @@ int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const dou
     pk.params = params;
     pk.qscale = qscale_of(law);
     pk.rec = base + lay.rec_off;
-    hipError_t e = launch_pack(pk, s);
+    hipError_t e = packed ? hipSuccess : launch_pack(pk, s);
     if (e != hipSuccess) return hip_fail(e, "pack");
 
+    if (fine) {
+        FineLaunch a = make_fine(FINE_FORCE, law, n, pot, base + lay.rec_off, base + lay.part_off);
+        a.epi = epi;
+        a.next = next;
+        a.next.rec = base + lay.rec_off;
+        a.next.rec_cols = (int)(rec_bytes(law->kind, law->precision) / (is_f32(law->precision) ? 4 : 8));
+        return run_fine(a, s, timed);
+    }
     if (sym) {
         SymLaunch a{};
         a.op = sym_op_of(law->kind);
@@ -1000,10 +1149,11 @@ int run_jerk(const nbody_law *law, const Cfg &c, const JerkPackLaunch &pk_in, co
 {
     // the symmetric tiles evaluate every row of the system (the callers pass them no row list)
     const bool sym = c.j_stage == kSymStage;
-    if (sym && (rows != nullptr || nrows != pk_in.n || !symjerk_ok(law->kind, law->precision) ||
-                pk_in.n > kSymJerkMaxN))
+    const bool fine = c.j_stage == kFineStage;
+    if ((sym || fine) && (rows != nullptr || nrows != pk_in.n || !symjerk_ok(law->kind, law->precision) ||
+                          pk_in.n > (fine ? fine_max_n(NBODY_API_JERK, law->kind, law->precision) : kSymJerkMaxN)))
         return fail(NBODY_EINVAL, "the symmetric jerk tiles evaluate whole systems of FP32 gravity only");
-    const int64_t npad = sym ? symjerk_npad(pk_in.n) : round_up(pk_in.n, 64);
+    const int64_t npad = sym ? symjerk_npad(pk_in.n) : (fine ? fine_npad(pk_in.n) : round_up(pk_in.n, 64));
     char *base = (char *)ws;
     JerkPackLaunch pk = pk_in;
     pk.prec = law->precision;
@@ -1011,6 +1161,13 @@ int run_jerk(const nbody_law *law, const Cfg &c, const JerkPackLaunch &pk_in, co
     pk.rec = base + lay.rec_off;
     hipError_t e = launch_pack_jerk(pk, s);
     if (e != hipSuccess) return hip_fail(e, "jerk pack");
+    if (fine) {
+        FineLaunch a = make_fine(FINE_JERK, law, pk_in.n, out_pot != nullptr, base + lay.rec_off, base + lay.part_off);
+        a.out_acc = out_acc;
+        a.out_jerk = out_jerk;
+        a.out_pot = out_pot;
+        return run_fine(a, s);
+    }
     if (sym) {
         SymJerkLaunch a{};
         a.prec = law->precision;
@@ -1082,7 +1239,7 @@ int jerk_impl(const double *pos, const double *vel, const double *mass, int64_t 
     const int64_t npad = round_up(std::max(n, ni), 64);
     Cfg c = sanitize(forced ? *forced : choose(NBODY_API_JERK, law, ni, 1, out_potential != nullptr, n),
                      NBODY_API_JERK, law->kind, law->precision, npad);
-    if (c.j_stage == kSymStage && (ilist || ni != n))   // the tiles take whole systems only
+    if (c.j_stage >= kSymStage && (ilist || ni != n))   // the tiles take whole systems only
         c = one_sided(c, NBODY_API_JERK, law, ni, n, out_potential != nullptr);
     JerkPackLaunch pk{};
     pk.n = n;
@@ -1097,7 +1254,8 @@ bool cfg_valid(const nbody_config *c)
     return c && c->block >= 64 && c->block <= (c->j_stage == kSymStage ? kSymThreads : 256) &&
            c->block % 64 == 0 && ipl_ok(c->i_per_lane) && c->j_tile >= 64 && c->j_tile % 64 == 0 &&
            c->j_tile <= (1 << 20) && c->j_split >= 1 && c->j_split <= kMaxSplit &&
-           (c->j_stage == 0 || c->j_stage == 1 || c->j_stage == kSymStage);
+           (c->j_stage == 0 || c->j_stage == 1 || c->j_stage == kSymStage ||
+            (c->j_stage == kFineStage && c->i_per_lane == kFineIch && c->j_tile == kFineRows));
 }
 
 Cfg from_abi(const nbody_config *c)
@@ -2145,6 +2303,17 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
         c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
                      law->precision, npad);
     }
+    if (c.j_stage == kFineStage) {
+        // likewise the fine tiles' records and slots
+        FwdWs lay{};
+        lay.part_off = align256((size_t)fine_npad(n) * rbytes);
+        lay.scratch_off = lay.total = kScratchBytes;
+        if (lay.part_off + fine_partial_bytes(n, FINE_FORCE, law->precision) <= kScratchBytes)
+            return run_forward(law, c, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot,
+                               base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
+        c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
+                     law->precision, npad);
+    }
     // the records first, then the split partials of the chosen j split, as far as they fit
     FwdWs lay{};
     lay.rec_off = 0;
@@ -2205,10 +2374,39 @@ int backward_impl(const double *pos, const double *params, int64_t n, const nbod
     rc = check_ws(ws, ws_bytes, lay.total);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    Cfg c = with_excl(sanitize(choose(NBODY_API_BACKWARD, law, n, 1, false), NBODY_API_BACKWARD, law->kind,
-                               law->precision, round_up(n, 64)),
-                      excl != nullptr);
+    Cfg c = sanitize(choose(NBODY_API_BACKWARD, law, n, 1, false), NBODY_API_BACKWARD, law->kind,
+                     law->precision, round_up(n, 64));
+    if (excl && c.j_stage == kFineStage)              // the fine tiles take no exclusion lists
+        c = sanitize(one_sided(c, NBODY_API_BACKWARD, law, n, n, false), NBODY_API_BACKWARD, law->kind,
+                     law->precision, round_up(n, 64));
+    c = with_excl(c, excl != nullptr);
     char *base = (char *)ws;
+    if (c.j_stage == kFineStage) {
+        AdjPackLaunch pk{};
+        pk.law = law->kind;
+        pk.prec = law->precision;
+        pk.n = n;
+        pk.npad = fine_npad(n);
+        pk.pos = pos;
+        pk.params = params;
+        pk.g = grad_force;
+        pk.qscale = qscale_of(law);
+        pk.rec = base + lay.rec_off;
+        hipError_t e = launch_pack_adjoint(pk, s);
+        if (e != hipSuccess) return hip_fail(e, "adjoint pack");
+        FineLaunch a = make_fine(fine_op_of(NBODY_API_BACKWARD, law->kind), law, n, false, pk.rec, base + lay.part_off);
+        a.params = params;
+        a.grad_pos = grad_pos;
+        a.grad_params = grad_params;
+        rc = run_fine(a, s);
+        if (rc) return rc;
+        if (types) {
+            e = launch_type_reduce(grad_params, types, n, n_types, grad_type_params,
+                                   (double *)(base + lay.type_off), kTypePartDoubles, s);
+            if (e != hipSuccess) return hip_fail(e, "per-type reduction");
+        }
+        return NBODY_OK;
+    }
     if (c.j_stage == kSymStage && law->kind == NBODY_LAW_LJC_LINEAR) {
         // LJC(linear)'s adjoint over unordered pairs (the position terms of the two atoms are
         // opposite, the charge, sigma and epsilon terms share one scalar): the batched adjoint's
@@ -2597,10 +2795,15 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
                            make_epi(law, (double *)(base + lay.scratch_off), out_potential), true, ws,
                            lay, s, nullptr);
     }
+    // The configurations of the steps: the last may ask for the potential.  With the fine tiles a
+    // step's reduction also does the next step's kick and drift and moves its records along.
+    const Cfg mid = choose(NBODY_API_LEAPFROG, law, n, 1, false);
+    const Cfg end = out_potential ? choose(NBODY_API_LEAPFROG, law, n, 1, true) : mid;
+    bool packed = false;
     for (int32_t k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
         const bool pot = last && out_potential;
-        const Cfg c = choose(NBODY_API_LEAPFROG, law, n, 1, pot);
+        const Cfg &c = last ? end : mid;
         PackLaunch pk{};
         pk.pos = pos;
         pk.kick_drift = 1;
@@ -2613,8 +2816,17 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
         epi.half_dt = 0.5 * dt;
         epi.vel = vel;
         epi.inv_mass = inv_mass;
-        rc = run_forward(law, c, pos, params, n, nullptr, n, epi, pot, ws, lay, s, &pk);
+        FineNext next{};
+        if (!last && c.j_stage == kFineStage && (k + 2 < nsteps ? mid : end).j_stage == kFineStage) {
+            next.on = 1;
+            next.half_dt = 0.5 * dt;
+            next.dt = dt;
+            next.pos = pos;
+        }
+        rc = run_forward(law, c, pos, params, n, nullptr, n, epi, pot, ws, lay, s, &pk, ExclArgs{}, true, 0, 1,
+                         packed, next);
         if (rc) return rc;
+        packed = next.on != 0;
     }
     return NBODY_OK;
 }
@@ -2645,14 +2857,19 @@ int hermite_step(double *pos, double *vel, double *acc, double *jerk, const doub
     hipStream_t s = (hipStream_t)stream;
     char *base = (char *)ws;
     double *a1 = (double *)(base + lay.a1_off), *j1 = (double *)(base + lay.j1_off);
-    Cfg c = sanitize(choose(NBODY_API_HERMITE, law, n, 1, false, n), NBODY_API_HERMITE, law->kind,
+    bool ruled_h, ruled_j;
+    Cfg c = sanitize(choose(NBODY_API_HERMITE, law, n, 1, false, n, &ruled_h), NBODY_API_HERMITE, law->kind,
                      law->precision, round_up(n, 64));
     c.j_split = hermite_split_table(law, n, c)->back();   // the block steps' rule for all n rows
     // a shared step evaluates every row: the symmetric tiles where the acceleration-and-jerk
-    // entry point's configuration for the whole system selects them
-    const Cfg cj = sanitize(choose(NBODY_API_JERK, law, n, 1, false, n), NBODY_API_JERK, law->kind,
-                            law->precision, round_up(n, 64));
-    if (cj.j_stage == kSymStage) c = cj;
+    // entry point's configuration for the whole system selects them, and by rule the fine tiles
+    // below their sizes (1.4x the one-sided step at 30,011 particles).  The acceleration-and-jerk
+    // entry point itself stays one-sided there: its results start block steps, whose individual
+    // steps jump with the last bits of the jerk, and the block steps' own evaluations are one-sided.
+    Cfg cj = choose(NBODY_API_JERK, law, n, 1, false, n, &ruled_j);
+    if (ruled_h && ruled_j && cj.j_stage < kSymStage && n >= kFineMinN) cj.j_stage = kFineStage;
+    cj = sanitize(cj, NBODY_API_JERK, law->kind, law->precision, round_up(n, 64));
+    if (cj.j_stage >= kSymStage) c = cj;
     for (int32_t k = 0; k < nsteps; ++k) {
         JerkPackLaunch pk{};
         pk.n = n;

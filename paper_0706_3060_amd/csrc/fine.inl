@@ -1,0 +1,602 @@
+// Fine pair tiles: every unordered pair {i, j} of one whole system once, its terms applied to both
+// particles (Newton's third law), in work units of 512 rows by 16 steps, for systems whose coarser
+// tiles would leave much of the chip idle and for FP64 pair arithmetic.
+//
+// Decomposition.  The rows form blocks of kFineChunks = 8 chunks of 64; a workgroup of four waves
+// holds one block in registers, two chunks a wave, and sweeps j chunks from the block's own onwards.
+// A sweep takes 64 steps: at step s lane l pairs its two i particles with particle j = l + s (mod
+// 64) of the chunk, which is staged twice in LDS so that each lane reads its record at a constant
+// offset.  The j sums travel with their particle from lane to lane (most through the LDS crossbar,
+// the last on the VALU by a DPP rotation: the two units share the moves); after the sweep the four
+// waves' j sums meet in LDS, are added in wave order, and leave as one row of the block's j slot.
+// Inside the block's own chunks, chunk k meets chunk q symmetrically when q > k, one-sidedly (i side
+// only, the own pair neutralised) when q == k, and not at all when q < k.
+//
+// Balance.  The sweeps of all blocks, in quarters of 16 steps, form one line that the launch cuts
+// into equal contiguous pieces, one per workgroup, so that every SIMD gets the same number of steps
+// (8,192 particles: 1,088 sweeps for 256 CUs, which whole sweeps would fill to 85 % and quarters
+// fill to 94 %).  A piece may begin inside a sweep: the j sums of such a sweep's rest go to the
+// workgroup's carry row.  A piece that crosses into the next block writes the i sums of the block it
+// leaves and loads the next.
+//
+// Sums.  i sums: FP32 partials of a sweep (64 steps) folded into Kahan or FP64 sums (FP64: plain FP64
+// partials folded with compensation); j sums: a sweep's terms (128 a wave, four waves).  Every slot
+// row is written once; k_fine_reduce adds a row's j slots, carries and i sums in a fixed order in
+// FP64 with compensation, so results repeat bit for bit.
+#include "allpairs.h"
+#include "fine.h"
+
+namespace nbk {
+namespace {
+
+constexpr int kQuarter = 16;                             // steps of a quarter sweep
+
+// ------------------------------------------------------------------ moves
+__device__ __forceinline__ float next_cross(int byte_addr, float v) { return from_next_lane(byte_addr, v); }
+__device__ __forceinline__ double next_cross(int byte_addr, double v)
+{
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, int2{__builtin_amdgcn_ds_bpermute(byte_addr, w.x),
+                                           __builtin_amdgcn_ds_bpermute(byte_addr, w.y)});
+}
+__device__ __forceinline__ float next_dpp(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x134, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double next_dpp(double v)
+{
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(double, int2{__builtin_amdgcn_mov_dpp(w.x, 0x134, 0xF, 0xF, false),
+                                           __builtin_amdgcn_mov_dpp(w.y, 0x134, 0xF, 0xF, false)});
+}
+
+// -------------------------------------------------------------- operators
+// Each: record type Rec (kCols values of T, of which the pair reads the first kStage), the sums NC per
+// particle, how many of them move through the crossbar, and the pair.  own marks the particle's own
+// pair, which contributes nothing; JS: add the j side.
+template <typename PT, bool POT> struct GravOp {
+    using T = PT;
+    struct alignas(16) Rec { T x, y, z, m; };
+    static constexpr int kCols = 4, kStage = 4, NC = POT ? 4 : 3, kCross = sizeof(T) == 8 ? 0 : 3;
+    template <bool JS>
+    static __device__ __forceinline__ void pair(const Rec &I, const Rec &J, const PairK<T> &k, bool own, T (&p)[NC],
+                                                T (&jv)[NC])
+    {
+        const T dx = J.x - I.x, dy = J.y - I.y, dz = J.z - I.z;
+        T r2 = fma_(dx, dx, k.eps2);
+        r2 = fma_(dy, dy, r2);
+        r2 = fma_(dz, dz, r2);
+        T mj = J.m;
+        r2 = own ? T(1) : r2;
+        mj = own ? T(0) : mj;
+        const T ri = rsqrt_(r2);
+        const T ri3 = (ri * ri) * ri;
+        const T cj = mj * ri3;
+        p[0] = fma_(cj, dx, p[0]);
+        p[1] = fma_(cj, dy, p[1]);
+        p[2] = fma_(cj, dz, p[2]);
+        if constexpr (POT) p[3] = fma_(mj, ri, p[3]);
+        if constexpr (JS) {
+            const T ci = I.m * ri3;
+            jv[0] = fma_(-ci, dx, jv[0]);
+            jv[1] = fma_(-ci, dy, jv[1]);
+            jv[2] = fma_(-ci, dz, jv[2]);
+            if constexpr (POT) jv[3] = fma_(I.m, ri, jv[3]);
+        }
+    }
+};
+
+template <typename PT, bool POT, int LAW> struct LjcOp {
+    using T = PT;
+    struct alignas(16) Rec { T x, y, z, qs, sh, se, p0, p1; };
+    static constexpr int kCols = 8, kStage = sizeof(T) == 8 ? 6 : 8, NC = POT ? 4 : 3, kCross = sizeof(T) == 8 ? 0 : 3;
+    template <bool JS>
+    static __device__ __forceinline__ void pair(const Rec &I, const Rec &J, const PairK<T> &k, bool own, T (&p)[NC],
+                                                T (&jv)[NC])
+    {
+        const T dx = J.x - I.x, dy = J.y - I.y, dz = J.z - I.z;
+        T r2 = dx * dx;
+        r2 = fma_(dy, dy, r2);
+        r2 = fma_(dz, dz, r2);
+        T qq = I.qs * J.qs;
+        T e = I.se * J.se;
+        r2 = own ? T(1) : r2;
+        qq = own ? T(0) : qq;
+        e = own ? T(0) : e;
+        T W, u = T(0);
+        ljc_terms<POT, LAW>(r2, qq, e, I.sh + J.sh, k, W, u);
+        p[0] = fma_(-W, dx, p[0]);
+        p[1] = fma_(-W, dy, p[1]);
+        p[2] = fma_(-W, dz, p[2]);
+        if constexpr (POT) p[3] += u;
+        if constexpr (JS) {
+            jv[0] = fma_(W, dx, jv[0]);
+            jv[1] = fma_(W, dy, jv[1]);
+            jv[2] = fma_(W, dz, jv[2]);
+            if constexpr (POT) jv[3] += u;
+        }
+    }
+};
+
+// Gravity's position adjoint: with w = m_i g_j - m_j g_i the term t = s^-3 (w - 3 s^-2 (d.w) d) of i
+// is minus that of j.
+struct HvpOp {
+    using T = float;
+    struct alignas(16) Rec { T x, y, z, m, gx, gy, gz, p0; };
+    static constexpr int kCols = 8, kStage = 8, NC = 3, kCross = 2;
+    template <bool JS>
+    static __device__ __forceinline__ void pair(const Rec &I, const Rec &J, const PairK<T> &k, bool own, T (&p)[NC],
+                                                T (&jv)[NC])
+    {
+        const T dx = J.x - I.x, dy = J.y - I.y, dz = J.z - I.z;
+        T r2 = fma_(dx, dx, k.eps2);
+        r2 = fma_(dy, dy, r2);
+        r2 = fma_(dz, dz, r2);
+        r2 = own ? 1.0f : r2;
+        T ri = rsqrt_(r2);
+        ri = own ? 0.0f : ri;
+        const T ri2 = ri * ri;
+        const T ri3 = ri2 * ri;
+        const T wx = fma_(-J.m, I.gx, I.m * J.gx);
+        const T wy = fma_(-J.m, I.gy, I.m * J.gy);
+        const T wz = fma_(-J.m, I.gz, I.m * J.gz);
+        T dw = dx * wx;
+        dw = fma_(dy, wy, dw);
+        dw = fma_(dz, wz, dw);
+        const T u = (ri2 * 3.0f) * dw;
+        const T t[3] = {fma_(-u, dx, wx), fma_(-u, dy, wy), fma_(-u, dz, wz)};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            p[c] = fma_(ri3, t[c], p[c]);
+            if constexpr (JS) jv[c] = fma_(-ri3, t[c], jv[c]);
+        }
+    }
+};
+
+// LJC(linear)'s adjoint: with u = g_j - g_i the position terms are opposite, and the charge, sigma
+// and epsilon terms share x (d.u); the derivatives are those of the one-sided adjoint kernel.
+struct LjcAdjOp {
+    using T = float;
+    struct alignas(16) Rec { T x, y, z, qs, sh, se, gx, gy, gz, p0, p1, p2; };
+    static constexpr int kCols = 16, kStage = 12, NC = 6, kCross = 5;
+    template <bool JS>
+    static __device__ __forceinline__ void pair(const Rec &I, const Rec &J, const PairK<T> &, bool own, T (&p)[NC],
+                                                T (&jv)[NC])
+    {
+        const T dx = J.x - I.x, dy = J.y - I.y, dz = J.z - I.z;
+        T r2 = dx * dx;
+        r2 = fma_(dy, dy, r2);
+        r2 = fma_(dz, dz, r2);
+        T qq = I.qs * J.qs;
+        T e = I.se * J.se;
+        r2 = own ? 1.0f : r2;
+        qq = own ? 0.0f : qq;
+        e = own ? 0.0f : e;
+        const T x = rcp_(r2);
+        const T sg = I.sh + J.sh;
+        const T sgx = sg * x;
+        const T s2 = sg * sgx;
+        const T s4 = s2 * s2;
+        const T s6 = s4 * s2;
+        const T lj = e * s6;
+        const T t = fma_(s6, 2.0f, -1.0f);
+        const T cx = qq * x;
+        const T W = fma_(lj, t, cx) * x;
+        const T wpr = fma_(lj, fma_(s6, 28.0f, -8.0f), cx * 4.0f) * (x * x);
+        const T ux = J.gx - I.gx, uy = J.gy - I.gy, uz = J.gz - I.gz;
+        T du = dx * ux;
+        du = fma_(dy, uy, du);
+        du = fma_(dz, uz, du);
+        du = own ? 0.0f : du;
+        const T tt = wpr * du;
+        const T v[3] = {fma_(tt, dx, -W * ux), fma_(tt, dy, -W * uy), fma_(tt, dz, -W * uz)};
+        const T xdu = x * du;
+        const T A = x * xdu;
+        const T B = ((e * (s4 * sgx)) * fma_(s6, 4.0f, -1.0f)) * xdu;
+        const T C = (s6 * t) * xdu;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p[c] += v[c];
+        p[3] = fma_(J.qs, A, p[3]);
+        p[4] += B;
+        p[5] = fma_(J.se, C, p[5]);
+        if constexpr (JS) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) jv[c] -= v[c];
+            jv[3] = fma_(I.qs, A, jv[3]);
+            jv[4] += B;
+            jv[5] = fma_(I.se, C, jv[5]);
+        }
+    }
+};
+
+// Acceleration and jerk: with w = v_j - v_i and u = w - 3 (d.w) d / s^2, i gets m_j d / s^3 and
+// m_j u / s^3, j the same with -m_i.
+template <bool POT> struct JerkOp {
+    using T = float;
+    struct alignas(16) Rec { T x, y, z, m, vx, vy, vz, p0; };
+    static constexpr int kCols = 8, kStage = 8, NC = POT ? 7 : 6, kCross = 4;
+    template <bool JS>
+    static __device__ __forceinline__ void pair(const Rec &I, const Rec &J, const PairK<T> &k, bool own, T (&p)[NC],
+                                                T (&jv)[NC])
+    {
+        const T dx = J.x - I.x, dy = J.y - I.y, dz = J.z - I.z;
+        const T wx = J.vx - I.vx, wy = J.vy - I.vy, wz = J.vz - I.vz;
+        T r2 = fma_(dx, dx, k.eps2);
+        r2 = fma_(dy, dy, r2);
+        r2 = fma_(dz, dz, r2);
+        T mj = J.m;
+        r2 = own ? 1.0f : r2;
+        mj = own ? 0.0f : mj;
+        const T ri = rsqrt_(r2);
+        const T ri2 = ri * ri;
+        const T ri3 = ri2 * ri;
+        T dw = dx * wx;
+        dw = fma_(dy, wy, dw);
+        dw = fma_(dz, wz, dw);
+        const T q = (dw * ri2) * -3.0f;
+        const T ux = fma_(q, dx, wx), uy = fma_(q, dy, wy), uz = fma_(q, dz, wz);
+        const T cj = mj * ri3;
+        p[0] = fma_(cj, dx, p[0]);
+        p[1] = fma_(cj, dy, p[1]);
+        p[2] = fma_(cj, dz, p[2]);
+        p[3] = fma_(cj, ux, p[3]);
+        p[4] = fma_(cj, uy, p[4]);
+        p[5] = fma_(cj, uz, p[5]);
+        if constexpr (POT) p[6] = fma_(mj, ri, p[6]);
+        if constexpr (JS) {
+            const T ci = I.m * ri3;
+            jv[0] = fma_(-ci, dx, jv[0]);
+            jv[1] = fma_(-ci, dy, jv[1]);
+            jv[2] = fma_(-ci, dz, jv[2]);
+            jv[3] = fma_(-ci, ux, jv[3]);
+            jv[4] = fma_(-ci, uy, jv[4]);
+            jv[5] = fma_(-ci, uz, jv[5]);
+            if constexpr (POT) jv[6] = fma_(I.m, ri, jv[6]);
+        }
+    }
+};
+
+// 128-bit vectors of a staged record
+template <class Op> constexpr int kVecs = Op::kStage * (int)sizeof(typename Op::T) / 16;
+
+template <class Op>
+__device__ __forceinline__ typename Op::Rec rec_from(const float4 *v, int stride)
+{
+    typename Op::Rec r;
+    float4 *o = (float4 *)&r;
+#pragma unroll
+    for (int k = 0; k < kVecs<Op>; ++k) o[k] = v[k * stride];
+    return r;
+}
+
+template <class Op, int NC = Op::NC, typename T = typename Op::T>
+__device__ __forceinline__ void move_on(int addr, T (&jv)[NC])
+{
+#pragma unroll
+    for (int c = 0; c < NC; ++c) jv[c] = c < Op::kCross ? next_cross(addr, jv[c]) : next_dpp(jv[c]);
+}
+
+// Steps s0 .. s1 - 1 of a sweep: the wave's i chunks before OWN against the chunk in `st`
+// symmetrically, i chunk OWN (when the wave has it: the chunk itself) one-sidedly.
+template <class Op, int OWN>
+__device__ __forceinline__ void fine_sweep(const float4 (&st)[kVecs<Op>][2 * kWave], int s0, int s1,
+                                           const typename Op::Rec (&iv)[kFineIch], const PairK<typename Op::T> &kc,
+                                           int addr, typename Op::T (&p)[kFineIch][Op::NC],
+                                           typename Op::T (&jv)[Op::NC])
+{
+    using R = typename Op::Rec;
+    const int lane = lane_id();
+    R J = rec_from<Op>(&st[0][lane + s0], 2 * kWave);
+    for (int s = s0; s < s1; s += kQuarter) {
+        const float4 *at = &st[0][lane + s + 1];
+#pragma unroll 8
+        for (int u = 0; u < kQuarter; ++u) {
+            // the next step's record, a step ahead (at most record 127 of the chunk staged twice)
+            const R next = rec_from<Op>(at + u, 2 * kWave);
+#pragma unroll
+            for (int k = 0; k < OWN; ++k) Op::template pair<true>(iv[k], J, kc, false, p[k], jv);
+            if constexpr (OWN < kFineIch) Op::template pair<false>(iv[OWN], J, kc, s + u == 0, p[OWN], jv);
+            if constexpr (OWN > 0) move_on<Op>(addr, jv);
+            J = next;
+        }
+    }
+}
+
+// the block of the quarter q: the last whose first quarter is at or before q
+__device__ __forceinline__ int fine_block(int q, int nb, int nch)
+{
+    int lo = 0, hi = nb - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (fine_begin(mid, nch) <= q) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// waves per SIMD the register allocation aims at
+template <class Op, int PREC> constexpr int fine_waves_per_eu()
+{
+    return sizeof(typename Op::T) == 8 || Op::NC >= 6 ? 3 : 4;
+}
+
+}  // namespace
+
+template <class Op, int PREC>
+__global__ __launch_bounds__(kFineWaves * kWave) __attribute__((amdgpu_waves_per_eu(fine_waves_per_eu<Op, PREC>())))
+void k_fine(FineLaunch a)
+{
+    using T = typename Op::T;
+    using R = typename Op::Rec;
+    constexpr int NC = Op::NC, NCP = NC > 4 ? 8 : 4, V = kVecs<Op>;
+    constexpr int RV = Op::kCols * (int)sizeof(T) / 16;         // vectors from record to record
+    constexpr int I = kFineIch;
+    __shared__ float4 st[2][V][2 * kWave];                      // the j chunk, staged twice, two buffers
+    __shared__ T jr[2][kFineWaves][kWave][NCP];                 // the waves' j sums of a sweep, two buffers
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nch = a.nch, nb = a.nb;
+    // the workgroups reach the XCDs in turn: each XCD takes a contiguous run of pieces
+    const int wg = (int)(blockIdx.x % kSymXcds) * (int)(gridDim.x / kSymXcds) + (int)(blockIdx.x / kSymXcds);
+    const int total = fine_begin(nb, nch);
+    if (wg >= a.nwg || (int64_t)wg * a.per >= total) return;    // whole workgroup
+    int q = wg * a.per;
+    const int qe = q + a.per < total ? q + a.per : total;
+    int b = fine_block(q, nb, nch);
+    int jc = b * kFineChunks + (q - fine_begin(b, nch)) / 4;
+    int s0 = (q % 4) * kQuarter;                                // fine_begin is a multiple of 4
+    const int64_t npad = (int64_t)nb * kFineRows;
+    const float4 *__restrict__ rec4 = (const float4 *)a.rec;
+    PairK<T> kc;
+    kc.eps2 = (T)a.eps2;
+    kc.za = (T)a.zeta[0];
+    kc.zb = (T)a.zeta[1];
+    kc.zc = (T)a.zeta[2];
+    kc.zd = (T)a.zeta[3];
+    kc.za3 = (T)(3.0 * a.zeta[0]);
+    kc.zb2 = (T)(2.0 * a.zeta[1]);
+    const int addr = ((lane + 1) & (kWave - 1)) * 4;
+
+    R iv[I];
+    RunSum<PREC> acc[I][NC];
+    T p[I][NC];
+    auto load_block = [&]() {
+#pragma unroll
+        for (int k = 0; k < I; ++k) {
+            iv[k] = rec_from<Op>(rec4 + ((int64_t)(b * kFineChunks + w * I + k) * kWave + lane) * RV, 1);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[k][c] = RunSum<PREC>{};
+        }
+    };
+    load_block();
+    // the first chunk: wave w stages vectors w, w + 4, ... of its 64 records
+    constexpr int VW = (V + kFineWaves - 1) / kFineWaves;
+    float4 g[VW];
+    auto fetch = [&](int c) {
+#pragma unroll
+        for (int k = 0; k < VW; ++k)
+            if (w + k * kFineWaves < V) g[k] = rec4[((int64_t)c * kWave + lane) * RV + w + k * kFineWaves];
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < VW; ++k)
+            if (w + k * kFineWaves < V) {
+                st[buf][w + k * kFineWaves][lane] = g[k];
+                st[buf][w + k * kFineWaves][lane + kWave] = g[k];
+            }
+    };
+    fetch(jc);
+    stage(0);
+    __syncthreads();
+    int buf = 0;
+    for (;;) {
+        const int s1 = s0 + (qe - q) * kQuarter < kWave ? s0 + (qe - q) * kQuarter : kWave;
+        q += (s1 - s0) / kQuarter;
+        // the sweep after this one
+        const bool more = q < qe;
+        const bool over = jc + 1 >= nch;                        // it begins the next block
+        const int jn = over ? (b + 1) * kFineChunks : jc + 1;
+        if (more) fetch(jn);
+        T jv[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) jv[c] = T(0);
+        const int rel = jc - (b * kFineChunks + w * I);         // chunk jc against i chunk k of the wave: rel - k
+        if (rel >= 0) {
+#pragma unroll
+            for (int k = 0; k < I; ++k)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) p[k][c] = T(0);
+            // rel >= I: the chunk after all of the wave's i chunks; otherwise the chunk is i chunk rel,
+            // and only the i chunks up to it meet it
+            if (rel >= I) fine_sweep<Op, I>(st[buf], s0, s1, iv, kc, addr, p, jv);
+            else if (rel == 1) fine_sweep<Op, 1>(st[buf], s0, s1, iv, kc, addr, p, jv);
+            else fine_sweep<Op, 0>(st[buf], s0, s1, iv, kc, addr, p, jv);
+#pragma unroll
+            for (int k = 0; k < I; ++k)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) acc[k][c].fold(p[k][c]);
+        }
+        // lane l holds the sums of j = l + s1
+#pragma unroll
+        for (int c = 0; c < NCP; ++c) jr[buf][w][(lane + s1) & (kWave - 1)][c] = c < NC ? jv[c < NC ? c : 0] : T(0);
+        if (more) stage(buf ^ 1);
+        // One barrier a sweep: the other buffers were last read in the sweep before, by waves that
+        // have all reached this barrier's predecessor.
+        __syncthreads();
+        {
+            T *dst = s0 == 0 ? (T *)a.jslot + ((int64_t)b * npad + (int64_t)jc * kWave) * NCP
+                             : (T *)a.carry + (int64_t)wg * kWave * NCP;
+            for (int e = threadIdx.x; e < kWave * NCP; e += kFineWaves * kWave) {
+                T v = (&jr[buf][0][0][0])[e];
+#pragma unroll
+                for (int x = 1; x < kFineWaves; ++x) v += (&jr[buf][x][0][0])[e];
+                dst[e] = v;
+            }
+        }
+        if (!more || over) {
+            T *dst = (T *)a.islot + (int64_t)(wg + b) * kFineRows * NCP;
+#pragma unroll
+            for (int k = 0; k < I; ++k)
+#pragma unroll
+                for (int c = 0; c < NCP; ++c)
+                    dst[((w * I + k) * kWave + lane) * NCP + c] = c < NC ? (T)acc[k][c < NC ? c : 0].value() : T(0);
+            if (!more) return;
+            ++b;
+            load_block();
+        }
+        jc = jn;
+        s0 = 0;
+        buf ^= 1;
+    }
+}
+
+// Column c of row r for each of 64 consecutive (row, column) pairs of a workgroup: the j slots of
+// blocks 0 .. r's own (with the carry of a sweep that two workgroups shared), then the i sums of r's
+// block by workgroup, the terms dealt out to the workgroup's eight waves (the smallest systems have
+// few rows and up to a hundred terms a row), each wave adding its own in order, and the waves' sums
+// merged in wave order, all in FP64 with compensation.  The operator's epilogue is separate for each
+// column.
+constexpr int kRedWaves = 8;
+template <typename T, int NCP>
+__global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
+{
+    __shared__ double part[kRedWaves][2][kWave];
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t t = (int64_t)blockIdx.x * kWave + lane;
+    const int64_t r = t / NCP;
+    const int c = (int)(t % NCP);
+    const int jc = (int)(blockIdx.x / NCP);                     // 64 (row, column) pairs lie in one chunk
+    const int b = jc / kFineChunks, nch = a.nch, per = a.per;
+    const int64_t cols = (int64_t)a.nb * kFineRows * NCP;
+    const T *__restrict__ jslot = (const T *)a.jslot + t;
+    const T *__restrict__ carry = (const T *)a.carry + (t - (int64_t)jc * kWave * NCP);
+    const T *__restrict__ islot = (const T *)a.islot + (t - (int64_t)b * kFineRows * NCP);
+    NSum v;
+    for (int k = w; k <= b; k += kRedWaves) {
+        const int q = fine_begin(k, nch) + 4 * (jc - k * kFineChunks);
+        const int last = (q + 3) / per;
+        v.add((double)jslot[k * cols]);
+        if (q / per != last) v.add((double)carry[(int64_t)last * kWave * NCP]);
+    }
+    const int w1 = (fine_begin(b + 1, nch) - 1) / per;
+#pragma unroll 4
+    for (int u = fine_begin(b, nch) / per + w; u <= w1; u += kRedWaves)
+        v.add((double)islot[(int64_t)(u + b) * kFineRows * NCP]);
+    part[w][0][lane] = v.s;
+    part[w][1][lane] = v.c;
+    __syncthreads();
+    if (w != 0) return;
+#pragma unroll
+    for (int u = 1; u < kRedWaves; ++u) v.merge(part[u][0][lane], part[u][1][lane]);
+    if (r >= a.n) return;
+    const double x = v.value();
+    switch (a.op) {
+    case FINE_FORCE: {
+        const Epilogue &e = a.epi;
+        if (c == 3) {
+            if (a.pot && e.out_pot) e.out_pot[r] = e.pscale * x;
+            return;
+        }
+        double f = e.fscale * x;
+        const int64_t i = 3 * r + c;
+        if (e.kick) {
+            f *= e.inv_mass ? e.inv_mass[r] : 1.0;
+            double u = e.vel[i] + e.half_dt * f;
+            if (a.next.on) {                             // the next step's kick and drift
+                u += a.next.half_dt * f;
+                const double y = a.next.pos[i] + a.next.dt * u;
+                a.next.pos[i] = y;
+                ((T *)a.next.rec)[r * a.next.rec_cols + c] = (T)y;
+            }
+            e.vel[i] = u;
+        }
+        e.out_force[i] = f;
+        return;
+    }
+    case FINE_HVP:
+        if (c < 3 && a.grad_pos) a.grad_pos[3 * r + c] = a.G * x;
+        return;
+    case FINE_LJC_ADJ:
+        if (c < 3) {
+            if (a.grad_pos) a.grad_pos[3 * r + c] = x;
+        } else if (c < 6 && a.grad_params) {
+            // the sums carry the records' factor 24 in eps (sigma) and sqrt(24) in se_j (epsilon)
+            const double k = c == 3 ? a.qscale : (c == 4 ? 3.0 : 12.0 / __builtin_sqrt(24.0 * a.params[3 * r + 2]));
+            a.grad_params[3 * r + c - 3] = k * x;
+        }
+        return;
+    default:
+        if (c < 3) a.out_acc[3 * r + c] = a.G * x;
+        else if (c < 6) a.out_jerk[3 * r + c - 3] = a.G * x;
+        else if (c == 6 && a.pot && a.out_pot) a.out_pot[r] = -a.G * x;
+    }
+}
+
+template <class Op, int PREC> static void fine_go(const FineLaunch &a, hipStream_t s)
+{
+    const int grid = (a.nwg + kSymXcds - 1) / kSymXcds * kSymXcds;
+    hipLaunchKernelGGL((k_fine<Op, PREC>), dim3((unsigned)grid), dim3(kFineWaves * kWave), 0, s, a);
+}
+template <class Op> static void fine_go32(const FineLaunch &a, hipStream_t s)
+{
+    if (a.prec == P_KAHAN) fine_go<Op, P_KAHAN>(a, s);
+    else fine_go<Op, P_FP64ACC>(a, s);
+}
+template <bool POT> static void fine_go_force(const FineLaunch &a, hipStream_t s)
+{
+    const bool d = a.prec == P_FP64;
+    switch (a.law) {
+    case GRAVITY: d ? fine_go<GravOp<double, POT>, P_FP64>(a, s) : fine_go32<GravOp<float, POT>>(a, s); return;
+    case LJC: d ? fine_go<LjcOp<double, POT, LJC>, P_FP64>(a, s) : fine_go32<LjcOp<float, POT, LJC>>(a, s); return;
+    case LJC_CONST:
+        d ? fine_go<LjcOp<double, POT, LJC_CONST>, P_FP64>(a, s) : fine_go32<LjcOp<float, POT, LJC_CONST>>(a, s);
+        return;
+    default: d ? fine_go<LjcOp<double, POT, LJC_SIG>, P_FP64>(a, s) : fine_go32<LjcOp<float, POT, LJC_SIG>>(a, s);
+    }
+}
+
+bool fine_supported(int op, int law, int prec)
+{
+    const bool f32 = prec == P_KAHAN || prec == P_FP64ACC;
+    switch (op) {
+    case FINE_FORCE: return f32 || prec == P_FP64;
+    case FINE_LJC_ADJ: return f32 && law == LJC;
+    default: return f32 && law == GRAVITY;
+    }
+}
+
+// a launch description that does not match the work of n particles is refused, never launched
+static bool fine_valid(const FineLaunch &a)
+{
+    if (!fine_supported(a.op, a.law, a.prec) || a.n <= 0 || a.n > kFineMaxN) return false;
+    if (a.nch != (int)((a.n + kWave - 1) / kWave) || a.nb != (a.nch + kFineChunks - 1) / kFineChunks) return false;
+    const int total = fine_begin(a.nb, a.nch);
+    return a.per >= 4 && a.nwg == (total + a.per - 1) / a.per && a.nwg <= kFineMaxWgs && a.rec && a.jslot &&
+           a.islot && a.carry;
+}
+
+hipError_t launch_fine(const FineLaunch &a, hipStream_t s)
+{
+    if (!fine_valid(a)) return hipErrorInvalidValue;
+    switch (a.op) {
+    case FINE_FORCE: a.pot ? fine_go_force<true>(a, s) : fine_go_force<false>(a, s); break;
+    case FINE_HVP: fine_go32<HvpOp>(a, s); break;
+    case FINE_LJC_ADJ: fine_go32<LjcAdjOp>(a, s); break;
+    default: a.pot ? fine_go32<JerkOp<true>>(a, s) : fine_go32<JerkOp<false>>(a, s);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_fine_reduce(const FineLaunch &a, hipStream_t s)
+{
+    if (!fine_valid(a)) return hipErrorInvalidValue;
+    const int cols = fine_cols(a.op);
+    const dim3 grid((unsigned)(a.nch * cols)), block(kRedWaves * kWave);
+    if (a.prec == P_FP64) hipLaunchKernelGGL((k_fine_reduce<double, 4>), grid, block, 0, s, a);
+    else if (cols == 4) hipLaunchKernelGGL((k_fine_reduce<float, 4>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_fine_reduce<float, 8>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace nbk

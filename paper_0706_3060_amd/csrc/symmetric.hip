@@ -458,3 +458,6 @@ hipError_t launch_sym_reduce(const SymLaunch &a, hipStream_t s)
 }
 
 }  // namespace nbk
+
+// The fine pair tiles: the same idea in smaller work units, part of this object.
+#include "fine.inl"
