@@ -155,7 +155,8 @@ typedef struct nbody_exclusions {
 } nbody_exclusions;
 
 /* Launch configuration of the all-pairs kernels (see nbody_set_config).
- *  block      threads per workgroup, a multiple of 64 in [64, 256];
+ *  block      threads per workgroup, a multiple of 64 in [64, 256] (512 with
+ *             j_stage 2, 1024 with j_stage 3);
  *  i_per_lane i-particles held in registers by each lane: 1, 2, 4 or 8
  *             (the i-unrolling of Section 3.3, "4x4" kernels);
  *  j_tile     j-particles per FP32 partial sum before it is folded into the
@@ -199,7 +200,12 @@ typedef struct nbody_exclusions {
  *             parts fill the chip's last round of tiles better and leave more
  *             slot partials for the reduction to read.  The requested value is
  *             rounded down to the nearest allowed one.
- *             3 = fine pair tiles, in one shape (block 256, i_per_lane 2, j_tile
+ *             3 = small systems.  With block 1024, i_per_lane 1 and j_tile
+ *             1024: row groups, one launch in which a workgroup finishes a few
+ *             rows on its own, for nbody_forces and leapfrog_step of up to 4,096
+ *             particles (not FP32_PLAIN); the rule's choice there (FP64 LJC: up
+ *             to 3,072 atoms, 2,304 with the sigmoidal dielectric).  Otherwise
+ *             fine pair tiles, in one shape (block 256, i_per_lane 2, j_tile
  *             512): each unordered pair of a whole system once, in quarter sweeps
  *             shared out equally over the workgroups; the rule's choice for
  *             FP32_KAHAN and FP32_FP64ACC from 2,048 to 32,767 particles (forces

@@ -66,6 +66,32 @@ __device__ __forceinline__ void store_pad(LjcRec<T> *rec, int64_t i)
     rec[i] = r;
 }
 
+// Column c (0..2 the force, 3 the potential) of a finished row's sums x: the scales, the leapfrog kick,
+// and with `next` the next step's kick and drift.  The columns of a row are independent.
+template <typename T>
+__device__ __forceinline__ void finish_column(const Epilogue &e, const StepNext &next, int64_t r, int c, double x,
+                                              bool pot)
+{
+    if (c == 3) {
+        if (pot && e.out_pot) e.out_pot[r] = e.pscale * x;
+        return;
+    }
+    double f = e.fscale * x;
+    const int64_t i = 3 * r + c;
+    if (e.kick) {
+        f *= e.inv_mass ? e.inv_mass[r] : 1.0;
+        double u = e.vel[i] + e.half_dt * f;
+        if (next.on) {
+            u += next.half_dt * f;
+            const double y = next.pos[i] + next.dt * u;
+            next.pos[i] = y;
+            ((T *)next.rec)[r * next.rec_cols + c] = (T)y;
+        }
+        e.vel[i] = u;
+    }
+    e.out_force[i] = f;
+}
+
 // ------------------------------------------------------- per-law i / j I/O ----
 template <typename T>
 __device__ __forceinline__ void load_i(const GravRec<T> *rec, int64_t p, GravI<T> &s)

@@ -174,6 +174,23 @@ int64_t fine_max_n(int api, int law, int prec)
     if (!fine_supported(fine_op_of(api, law), law, prec)) return 0;
     return is_f32(prec) ? kSymMinN : kFineMaxN;
 }
+// Row groups (rows.inl): small systems' forces and leapfrog steps in one launch each, reported as
+// j_stage 3 with the workgroup of 1,024 threads.  The rule's line, per call against the fine tiles
+// (us): at 4,096 particles FP32 gravity 14 against 20, LJC(linear) 18 against 22, LJC(sigmoidal) 25
+// against 27, FP64 gravity 19 against 23; at 5,000 FP32 gravity 23 against 20.  One-sided FP64 LJC
+// pairs cost more: LJC(linear) 22 against 22 at 3,000, LJC(sigmoidal) 26 against 29 at 2,050 and 34
+// against 29 at 3,000.  (Three launches of the one-sided kernels: 20-21 at any size below 2,000.)
+constexpr int kRowsBlock = 1024;
+int64_t rows_rule_n(int law, int prec)
+{
+    if (is_f32(prec) || law == NBODY_LAW_GRAVITY) return kRowsMaxN;
+    return law == NBODY_LAW_LJC_SIGMOIDAL ? 2304 : 3072;
+}
+int64_t rows_max_n(int api, int prec)
+{
+    if (api != NBODY_API_FORCES && api != NBODY_API_LEAPFROG) return 0;
+    return prec == NBODY_FP32_PLAIN ? 0 : kRowsMaxN;
+}
 int fine_chunks(int64_t n) { return (int)((std::max<int64_t>(n, 1) + 63) / 64); }
 int fine_blocks(int64_t n) { return (fine_chunks(n) + kFineChunks - 1) / kFineChunks; }
 int64_t fine_npad(int64_t n) { return (int64_t)fine_blocks(n) * kFineRows; }
@@ -341,6 +358,12 @@ Cfg sanitize(Cfg c, int api, int law, int prec, int64_t npad)
         c.j_stage = 1;                                  // other laws, precisions, entry points, sizes
     }
     if (c.j_stage == kFineStage) {
+        if (c.block == kRowsBlock && npad <= rows_max_n(api, prec)) {
+            c.ipl = 1;
+            c.j_tile = 1024;
+            c.j_split = 1;
+            return c;
+        }
         if (npad <= fine_max_n(api, law, prec)) {
             c.block = kFineWaves * 64;                    // the fine tiles' one shape
             c.ipl = kFineIch;
@@ -504,6 +527,11 @@ Cfg heuristic(int api, int law, int prec, int64_t n, int64_t nj, int64_t S, bool
         return sanitize(c, api, law, prec, round_up(n, 64));
     }
     const int64_t npad = round_up(std::max<int64_t>(std::max(n, nj), 1), 64);
+    if (allow_sym && n == nj && n <= rows_rule_n(law, prec) && n <= rows_max_n(api, prec)) {
+        c.j_stage = kFineStage;
+        c.block = kRowsBlock;
+        return sanitize(c, api, law, prec, npad);
+    }
     if (allow_sym && n == nj && n >= kFineMinN && npad <= fine_max_n(api, law, prec) &&
         !(api == NBODY_API_BACKWARD && law == NBODY_LAW_LJC_LINEAR && (n < kFineAdjLjcMinN || n >= kSymAdjLjcMinN)) &&
         api != NBODY_API_JERK) {
@@ -723,6 +751,8 @@ FwdWs fwd_layout(int api, const nbody_law *law, int64_t n)
         nrec = std::max(nrec, fine_npad(n));
         part = std::max(part, fine_partial_bytes(n, FINE_FORCE, law->precision));
     }
+    // the row groups' leapfrog steps keep a second buffer of records
+    if (npad <= rows_max_n(api, law->precision)) part = std::max(part, (size_t)npad * rec_bytes(law->kind, law->precision));
     size_t off = 0;
     w.rec_off = off;
     off = align256(off + (size_t)nrec * rec_bytes(law->kind, law->precision));
@@ -1036,12 +1066,62 @@ int run_fine(const FineLaunch &a, hipStream_t s, bool timed = true)
     return NBODY_OK;
 }
 
+// Rows of a workgroup of the row groups: eight (four are 5 % slower at 600 and 1,000 particles), or as
+// many more as leave a workgroup to a CU
+int rows_of(int64_t n)
+{
+    int r = 8;
+    while (r < 32 && (n + r - 1) / r > device_cus()) r *= 2;
+    return r;
+}
+
+// One launch for the forces of a small system.  A leapfrog step (pk_in) reads packed records: the first
+// step's come from the pack, the others from the step before; the two buffers alternate by next.rec.
+int run_rows(const nbody_law *law, const double *pos, const double *params, int64_t n, const Epilogue &epi, bool pot,
+             char *base, const FwdWs &lay, hipStream_t s, const PackLaunch *pk_in, bool timed, bool packed,
+             const StepNext &next)
+{
+    RowLaunch a{};
+    a.law = law->kind;
+    a.prec = law->precision;
+    a.pot = pot ? 1 : 0;
+    a.rows = rows_of(n);
+    a.n = n;
+    a.eps2 = law->kind == NBODY_LAW_GRAVITY ? law->softening * law->softening : 0.0;
+    for (int c = 0; c < 4; ++c) a.zeta[c] = law->kind == NBODY_LAW_LJC_SIGMOIDAL ? law->zeta[c] : 0.0;
+    a.qscale = qscale_of(law);
+    a.pos = pos;
+    a.params = params;
+    a.epi = epi;
+    a.next = next;
+    if (pk_in) {
+        PackLaunch pk = *pk_in;
+        pk.law = law->kind;
+        pk.prec = law->precision;
+        pk.n = pk.npad = n;
+        pk.params = params;
+        pk.qscale = qscale_of(law);
+        if (!pk.rec) pk.rec = base + lay.rec_off;
+        a.rec = pk.rec;
+        a.next.rec = pk.rec == base + lay.rec_off ? base + lay.part_off : base + lay.rec_off;
+        a.next.rec_cols = (int)(rec_bytes(law->kind, law->precision) / (is_f32(law->precision) ? 4 : 8));
+        if (!packed) {
+            const hipError_t e = launch_pack(pk, s);
+            if (e != hipSuccess) return hip_fail(e, "pack");
+        }
+    }
+    Timer t(s, timed);
+    const hipError_t e = launch_rows(a, s);
+    t.stop();
+    return e == hipSuccess ? NBODY_OK : hip_fail(e, "row groups");
+}
+
 // pack + all-pairs (+ split reduction) for one system already validated
 int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const double *params,
                 int64_t n, const int64_t *rows, int64_t nrows, const Epilogue &epi, bool pot,
                 void *ws, const FwdWs &lay, hipStream_t s, PackLaunch *pk_in,
                 const ExclArgs &excl = ExclArgs{}, bool timed = true, int64_t share = 0,
-                int64_t n_shares = 1, bool packed = false, const FineNext &next = FineNext{})
+                int64_t n_shares = 1, bool packed = false, const StepNext &next = StepNext{})
 {
     // the symmetric tiles (j_stage 2) evaluate whole systems; sanitize admits the
     // configuration only for FP32_KAHAN / FP32_FP64ACC forward laws and gravity's backward
@@ -1050,6 +1130,7 @@ int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const dou
     const bool fine = c.j_stage == kFineStage && rows == nullptr && nrows == n && excl.off == nullptr;
     const int64_t npad = sym ? sym_npad(n, blk) : (fine ? fine_npad(n) : round_up(n, 64));
     char *base = (char *)ws;
+    if (fine && c.block == kRowsBlock) return run_rows(law, pos, params, n, epi, pot, base, lay, s, pk_in, timed, packed, next);
     PackLaunch pk{};
     if (pk_in) pk = *pk_in;
     pk.law = law->kind;
@@ -1251,11 +1332,12 @@ int jerk_impl(const double *pos, const double *vel, const double *mass, int64_t 
 
 bool cfg_valid(const nbody_config *c)
 {
-    return c && c->block >= 64 && c->block <= (c->j_stage == kSymStage ? kSymThreads : 256) &&
+    const bool rows = c && c->j_stage == kFineStage && c->block == kRowsBlock && c->i_per_lane == 1 && c->j_tile == 1024;
+    return c && c->block >= 64 && (rows || c->block <= (c->j_stage == kSymStage ? kSymThreads : 256)) &&
            c->block % 64 == 0 && ipl_ok(c->i_per_lane) && c->j_tile >= 64 && c->j_tile % 64 == 0 &&
            c->j_tile <= (1 << 20) && c->j_split >= 1 && c->j_split <= kMaxSplit &&
            (c->j_stage == 0 || c->j_stage == 1 || c->j_stage == kSymStage ||
-            (c->j_stage == kFineStage && c->i_per_lane == kFineIch && c->j_tile == kFineRows));
+            (c->j_stage == kFineStage && (rows || (c->i_per_lane == kFineIch && c->j_tile == kFineRows))));
 }
 
 Cfg from_abi(const nbody_config *c)
@@ -2308,7 +2390,7 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
         FwdWs lay{};
         lay.part_off = align256((size_t)fine_npad(n) * rbytes);
         lay.scratch_off = lay.total = kScratchBytes;
-        if (lay.part_off + fine_partial_bytes(n, FINE_FORCE, law->precision) <= kScratchBytes)
+        if (c.block == kRowsBlock || lay.part_off + fine_partial_bytes(n, FINE_FORCE, law->precision) <= kScratchBytes)
             return run_forward(law, c, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot,
                                base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
         c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
@@ -2799,7 +2881,7 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
     // step's reduction also does the next step's kick and drift and moves its records along.
     const Cfg mid = choose(NBODY_API_LEAPFROG, law, n, 1, false);
     const Cfg end = out_potential ? choose(NBODY_API_LEAPFROG, law, n, 1, true) : mid;
-    bool packed = false;
+    bool packed = false, other = false;
     for (int32_t k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
         const bool pot = last && out_potential;
@@ -2816,8 +2898,12 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
         epi.half_dt = 0.5 * dt;
         epi.vel = vel;
         epi.inv_mass = inv_mass;
-        FineNext next{};
-        if (!last && c.j_stage == kFineStage && (k + 2 < nsteps ? mid : end).j_stage == kFineStage) {
+        StepNext next{};
+        // the row groups alternate between two record buffers
+        other = packed && !other;
+        if (packed && c.block == kRowsBlock) pk.rec = base + (other ? lay.part_off : lay.rec_off);
+        const Cfg &after = k + 2 < nsteps ? mid : end;
+        if (!last && c.j_stage == kFineStage && after.j_stage == kFineStage && after.block == c.block) {
             next.on = 1;
             next.half_dt = 0.5 * dt;
             next.dt = dt;

@@ -28,13 +28,6 @@ __host__ __device__ inline int fine_cols(int op) { return op == FINE_LJC_ADJ || 
 // fine_begin(nb, nch) quarters that the workgroups share out in equal contiguous pieces.
 __host__ __device__ inline int fine_begin(int b, int nch) { return 4 * (b * nch - kFineChunks * (b * (b - 1) / 2)); }
 
-struct FineNext {                  // a leapfrog step's kick and drift after the one just finished
-    int on;
-    double half_dt, dt;
-    double *pos;                   // [n][3]
-    void *rec;                     // the records whose positions move along (row stride rec_cols)
-    int rec_cols;
-};
 struct FineLaunch {
     int op, law, prec, pot;
     int64_t n;
@@ -47,7 +40,7 @@ struct FineLaunch {
     void *islot;                   // [nwg + nb][kFineRows][cols] i sums of workgroup w in block b: w + b
     void *carry;                   // [nwg][64][cols] j sums of a sweep that began in the workgroup before
     Epilogue epi;                  // FINE_FORCE
-    FineNext next;
+    StepNext next;
     double G, qscale;              // the adjoints and the jerk
     const double *params;
     double *grad_pos, *grad_params;

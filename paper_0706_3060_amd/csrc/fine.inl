@@ -492,28 +492,7 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
     if (r >= a.n) return;
     const double x = v.value();
     switch (a.op) {
-    case FINE_FORCE: {
-        const Epilogue &e = a.epi;
-        if (c == 3) {
-            if (a.pot && e.out_pot) e.out_pot[r] = e.pscale * x;
-            return;
-        }
-        double f = e.fscale * x;
-        const int64_t i = 3 * r + c;
-        if (e.kick) {
-            f *= e.inv_mass ? e.inv_mass[r] : 1.0;
-            double u = e.vel[i] + e.half_dt * f;
-            if (a.next.on) {                             // the next step's kick and drift
-                u += a.next.half_dt * f;
-                const double y = a.next.pos[i] + a.next.dt * u;
-                a.next.pos[i] = y;
-                ((T *)a.next.rec)[r * a.next.rec_cols + c] = (T)y;
-            }
-            e.vel[i] = u;
-        }
-        e.out_force[i] = f;
-        return;
-    }
+    case FINE_FORCE: finish_column<T>(a.epi, a.next, r, c, x, a.pot != 0); return;
     case FINE_HVP:
         if (c < 3 && a.grad_pos) a.grad_pos[3 * r + c] = a.G * x;
         return;

@@ -403,3 +403,6 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s)
 }
 
 }  // namespace nbk
+
+// Small systems in one launch, part of this object.
+#include "rows.inl"

@@ -38,6 +38,16 @@ struct Epilogue {
     const double *inv_mass;     // [rows] or null
 };
 
+// A leapfrog step's kick and drift after the one that an epilogue finishes, and the records that the
+// next step reads (their positions move along).
+struct StepNext {
+    int on;
+    double half_dt, dt;
+    double *pos;                 // [rows][3]
+    void *rec;
+    int rec_cols;                // values from record to record
+};
+
 struct FwdLaunch {
     int law, prec, ipl, pot;     // template selectors
     int block;                   // threads per workgroup
@@ -71,6 +81,22 @@ struct PackLaunch {
     const double *acc;
     double half_dt, dt;
 };
+
+// ---- row groups (rows.inl): the forces of a small system, or a leapfrog step, in one launch ----
+constexpr int64_t kRowsMaxN = 4096;
+struct RowLaunch {
+    int law, prec, pot;
+    int rows;                    // rows of a workgroup: 1, 2, 4 .. 32
+    int64_t n;
+    double eps2;
+    double zeta[4];
+    const void *rec;             // packed records [n], or null: made from pos and params
+    const double *pos, *params;
+    double qscale;
+    Epilogue epi;
+    StepNext next;               // with rec: next.rec is another buffer
+};
+hipError_t launch_rows(const RowLaunch &a, hipStream_t s);
 
 hipError_t launch_pack(const PackLaunch &p, hipStream_t s);
 hipError_t launch_forces(const FwdLaunch &f, hipStream_t s);

@@ -1,8 +1,9 @@
-"""GPU parity of the fine pair tiles (j_stage 3: each unordered pair of one system once, in quarter
-sweeps shared out equally over the workgroups) against the FP64 oracle.
+"""GPU parity of the small systems' kernels (j_stage 3) against the FP64 oracle: the fine pair tiles
+(each unordered pair of one system once, in quarter sweeps shared out equally over the workgroups) and
+the row groups (a workgroup finishes a few rows in one launch).
 
 Sizes around the edges of a chunk (64 records) and a block (512), and sizes whose pieces begin inside
-a sweep and cross blocks; every law and precision of the forces, both adjoints, the acceleration and
+a sweep and cross blocks, for the row groups those of an LDS tile (1,024); every law and precision of the forces, both adjoints, the acceleration and
 jerk.  A pair counted twice or missed is an error of order one in its rows.  Bars: FP64 1e-12 of the
 largest value (adjoint-free paths); FP32 a median of 1e-5 and a maximum of 1e-3, on inputs rounded as
 the records round them.
@@ -16,7 +17,8 @@ from paper_0706_3060_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-FINE = (256, 2, 512, 1, 3)
+FINE, ROWS = (256, 2, 512, 1, 3), (1024, 1, 1024, 1, 3)
+ROW_SIZES = [1, 2, 7, 65, 1000, 1023, 1025, 2051, 4096]
 SIZES = [1, 2, 63, 65, 511, 512, 513, 1025, 2049, 5003]
 ZC = (2.0e-4, -6.0e-3, 0.25, 0.4)
 EPS, G = 0.01, 1.3
@@ -71,10 +73,11 @@ def seen(prec, a):
     return a if prec == "fp64" else W.round_to_f32(a)
 
 
-@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("cfg,n", [(FINE, n) for n in SIZES] + [(ROWS, n) for n in ROW_SIZES])
 @pytest.mark.parametrize("prec", ["fp64", "fp32_kahan", "fp32_fp64acc"])
-def test_forces_of_every_law(fine, prec, n):
+def test_forces_of_every_law(fine, prec, cfg, n):
     nb = fine
+    nb.set_config(nb.API_FORCES, *cfg)
     x, _, m = sphere(n, 900 + n)
     s = atoms(n, 800 + n)
     runs = [(nb.gravity(prec, softening=EPS, G=G), x, m,
@@ -85,7 +88,8 @@ def test_forces_of_every_law(fine, prec, n):
     runs.append((nb.ljc_sigmoidal(ZC, prec), s.pos, s.params(),
                  lambda: oracle.ljc_sigmoidal(xs, s.q, s.sigma, s.epsilon, ZC)))
     for law, pos, par, ref in runs:
-        assert nb.get_config(nb.API_FORCES, n, law)["j_stage"] == 3
+        c = nb.get_config(nb.API_FORCES, n, law)
+        assert (c["block"], c["i_per_lane"], c["j_tile"], c["j_split"], c["j_stage"]) == cfg
         f, u = nb.forces(dev(pos), dev(par), law)
         f1, u1 = nb.forces(dev(pos), dev(par), law)
         f2, _ = nb.forces(dev(pos), dev(par), law, potential=False)
@@ -123,10 +127,13 @@ def test_adjoints_and_jerk(fine, prec, n):
     assert (np.abs(gt.cpu().numpy() - sums) <= 1e-3 * scale + 1e-300).all()
 
 
-@pytest.mark.parametrize("law,prec", [("gravity", "fp64"), ("gravity", "fp32_kahan"), ("ljc", "fp32_fp64acc")])
-def test_steps_in_one_call_are_the_steps_one_by_one(fine, law, prec):
-    """A step's reduction kicks and drifts for the next step: the same arithmetic as separate calls."""
+@pytest.mark.parametrize("cfg", [FINE, ROWS])
+@pytest.mark.parametrize("law,prec", [("gravity", "fp64"), ("gravity", "fp32_kahan"), ("ljc", "fp32_fp64acc"),
+                                      ("ljc", "fp64")])
+def test_steps_in_one_call_are_the_steps_one_by_one(fine, law, prec, cfg):
+    """A step's last kernel kicks and drifts for the next step: the same arithmetic as separate calls."""
     nb = fine
+    nb.set_config(nb.API_LEAPFROG, *cfg)
     n = 1333
     if law == "gravity":
         x, v, par = sphere(n, 51)
@@ -148,7 +155,7 @@ def test_steps_in_one_call_are_the_steps_one_by_one(fine, law, prec):
 def test_rule_round_trip_and_allocation_free_call(nb):
     """The rule takes the fine tiles between the smallest systems and the coarser tiles, and for FP64; the
     reported configuration can be set; the allocation-free call gives the same sums."""
-    for prec, n, want in [("fp32_kahan", 9000, True), ("fp32_kahan", 32768, False), ("fp64", 9000, True),
+    for prec, n, want in [("fp32_kahan", 64, True), ("fp32_kahan", 4097, True), ("fp32_kahan", 9000, True), ("fp32_kahan", 32768, False), ("fp64", 9000, True),
                           ("fp64", 1 << 18, True), ("fp64", (1 << 18) + 1, False)]:
         c = nb.get_config(nb.API_FORCES, n, nb.gravity(prec))
         assert (c["j_stage"] == 3) == want, (prec, n, c)
@@ -156,8 +163,9 @@ def test_rule_round_trip_and_allocation_free_call(nb):
             nb.set_config(nb.API_FORCES, **c)
             nb.clear_config(nb.API_FORCES)
     for prec in ("fp64", "fp32_kahan"):
-        x, _, m = sphere(9000, 61)
-        law = nb.gravity(prec, softening=EPS)
-        f, u = nb.forces(dev(x), dev(m), law)
-        f1, u1 = nb.forces_noalloc(dev(x), dev(m), law)
-        assert torch.equal(f, f1) and torch.equal(u, u1)
+        for n in (1000, 9000):
+            x, _, m = sphere(n, 61)
+            law = nb.gravity(prec, softening=EPS)
+            f, u = nb.forces(dev(x), dev(m), law)
+            f1, u1 = nb.forces_noalloc(dev(x), dev(m), law)
+            assert torch.equal(f, f1) and torch.equal(u, u1)
