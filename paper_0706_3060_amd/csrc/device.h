@@ -317,21 +317,57 @@ __device__ __forceinline__ void split_group_sum(const double *__restrict__ parti
 #pragma unroll
                 for (int c = 0; c < NC; ++c) v[c].add(x[u][c]);
         }
+        // (two for the splits of up to 2 G parts)
+        for (; s + G < nsplit; s += 2 * G) {
+            double x[2][NC];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) x[u][c] = partial[(s + u * G) * part_stride + r * width + c];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) v[c].add(x[u][c]);
+        }
         for (; s < nsplit; s += G) {
             const double *o = partial + s * part_stride + r * width;
 #pragma unroll
             for (int c = 0; c < NC; ++c) v[c].add(o[c]);
         }
     }
-    for (int m = 1; m < G; m <<= 1)
+    if (G == 1) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const double s2 = __shfl_xor(v[c].s, m);
-            const double c2 = __shfl_xor(v[c].c, m);
-            v[c].merge(s2, c2);
+        for (int c = 0; c < NC; ++c) out[c] = v[c].value();
+        return;
+    }
+    // The butterfly over the lanes q ^ 1, q ^ 2, ...  At its first step each lane gives its partner one
+    // half of the columns and goes on with the other: the merge is commutative bit for bit, so the
+    // partner's result would be the same, and half the lane exchanges and additions remain.
+    constexpr int H = (NC + 1) / 2;
+    const bool up = (q & 1) != 0;                    // this lane keeps columns H .. NC - 1
+    NSum h[H];
+#pragma unroll
+    for (int c = 0; c < H; ++c) {
+        const int d = c + H < NC ? c + H : c;        // (NC odd: column c once more, unused)
+        const NSum keep = up ? v[d] : v[c], give = up ? v[c] : v[d];
+        h[c] = keep;
+        const double s2 = __shfl_xor(give.s, 1);
+        const double c2 = __shfl_xor(give.c, 1);
+        h[c].merge(s2, c2);
+    }
+    for (int m = 2; m < G; m <<= 1)
+#pragma unroll
+        for (int c = 0; c < H; ++c) {
+            const double s2 = __shfl_xor(h[c].s, m);
+            const double c2 = __shfl_xor(h[c].c, m);
+            h[c].merge(s2, c2);
         }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) out[c] = v[c].value();
+    for (int c = 0; c < H; ++c) {
+        const double own = h[c].value(), other = __shfl_xor(own, 1);
+        out[c] = up ? other : own;
+        if (c + H < NC) out[c + H] = up ? own : other;
+    }
 }
 
 // wave-uniform "any lane" (result lives in an SGPR)
