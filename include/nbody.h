@@ -205,14 +205,18 @@ typedef struct nbody_exclusions {
  *             rows on its own, for nbody_forces and leapfrog_step of up to 4,096
  *             particles (not FP32_PLAIN); the rule's choice there (FP64 LJC: up
  *             to 3,072 atoms, 2,304 with the sigmoidal dielectric).  Otherwise
- *             fine pair tiles, in one shape (block 256, i_per_lane 2, j_tile
- *             512): each unordered pair of a whole system once, in quarter sweeps
- *             shared out equally over the workgroups; the rule's choice for
- *             FP32_KAHAN and FP32_FP64ACC from 2,048 to 32,767 particles (forces
- *             and leapfrog of every law, gravity's backward, LJC(linear)'s from
- *             2,560 to 16,383 atoms, the shared Hermite steps), and for the
- *             forces and leapfrog of every law in FP64 from 2,048 to 262,144
- *             particles. */
+ *             fine pair tiles (block 256, i_per_lane 2 or 4, j_tile 256 times
+ *             that; 4 for the forces in FP64 and of gravity in FP32): each
+ *             unordered pair of a whole system once, in quarter sweeps shared out
+ *             equally over the workgroups, for up to 131,072 particles
+ *             (FP32_KAHAN, FP32_FP64ACC) or 262,144 (FP64, forces and leapfrog).
+ *             The rule's choice above the row groups: for FP32 up to 32,767
+ *             particles (forces and leapfrog of every law, gravity's backward,
+ *             LJC(linear)'s from 2,560 to 16,383 atoms, the shared Hermite
+ *             steps), for FP64 everywhere it applies.  Where the rule reports
+ *             j_stage 2, up to 65,536 particles, a launch whose configuration is
+ *             neither forced nor tuned runs them too (not the jerk and
+ *             LJC(linear)'s backward). */
 typedef struct nbody_config {
     int32_t block;
     int32_t i_per_lane;

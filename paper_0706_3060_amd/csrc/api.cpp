@@ -158,7 +158,18 @@ size_t symadj_ljc_partial_bytes(int64_t n)
 // particles the coarser tiles do as well (within 3 % at 50,001) with fewer slots.
 constexpr int kFineStage = 3;
 constexpr int64_t kFineMinN = 2048;
+constexpr int64_t kFineMaxN32 = int64_t(1) << 17;
 constexpr int64_t kFineAdjLjcMinN = 2560;
+// Four i chunks a wave halve the j sums' moves a pair, which two make up for in balance below (FP64
+// gravity with potentials: 52 us with two chunks against 55 at 8,192 particles, 163 against 162 at
+// 18,000, 425 against 397 at 30,011, 1,147 against 1,075 at 50,001, 7,973 against 7,273 at 131,072; FP32
+// without them 52 against 55 at 12,000, 94 against 91 at 18,000, 213 against 201 at 30,011).
+constexpr int64_t kFineMin4 = 20480;
+// Where the rule says the coarser tiles (j_stage 2), the fine tiles still run up to this size: against
+// them per call (us) at 33,000 particles LJC(linear) with energies 385 against 451, gravity's adjoint
+// 380 against 447; at 65,536 gravity 871 against 889 (963 against 964 with potentials), LJC(linear)
+// with energies 1,427 against 1,453, without 1,234 against 1,261, gravity's adjoint 1,408 against 1,460.
+constexpr int64_t kFineForSym = int64_t(1) << 16;
 bool sym_eligible(int api, int law, int prec);
 int fine_op_of(int api, int law)
 {
@@ -172,7 +183,7 @@ int64_t fine_max_n(int api, int law, int prec)
     if (api != NBODY_API_FORCES && api != NBODY_API_LEAPFROG && api != NBODY_API_BACKWARD && api != NBODY_API_JERK)
         return 0;
     if (!fine_supported(fine_op_of(api, law), law, prec)) return 0;
-    return is_f32(prec) ? kSymMinN : kFineMaxN;
+    return is_f32(prec) ? kFineMaxN32 : kFineMaxN;
 }
 // Row groups (rows.inl): small systems' forces and leapfrog steps in one launch each, reported as
 // j_stage 3 with the workgroup of 1,024 threads.  The rule's line, per call against the fine tiles
@@ -192,27 +203,35 @@ int64_t rows_max_n(int api, int prec)
     return prec == NBODY_FP32_PLAIN ? 0 : kRowsMaxN;
 }
 int fine_chunks(int64_t n) { return (int)((std::max<int64_t>(n, 1) + 63) / 64); }
-int fine_blocks(int64_t n) { return (fine_chunks(n) + kFineChunks - 1) / kFineChunks; }
-int64_t fine_npad(int64_t n) { return (int64_t)fine_blocks(n) * kFineRows; }
+int fine_blocks(int64_t n, int ich) { return (fine_chunks(n) + kFineWaves * ich - 1) / (kFineWaves * ich); }
+int64_t fine_npad(int64_t n, int ich) { return (int64_t)fine_blocks(n, ich) * kFineWaves * ich * 64; }
+int fine_quarters(int64_t n, int ich) { return fine_begin(fine_blocks(n, ich), fine_chunks(n), kFineWaves * ich); }
 // most workgroups a launch over n particles has: four quarters of a sweep each at least
-int fine_wgs_bound(int64_t n)
-{
-    return std::min(kFineMaxWgs, (fine_begin(fine_blocks(n), fine_chunks(n)) + 3) / 4);
-}
+int fine_wgs_bound(int64_t n, int ich) { return std::min(kFineMaxWgs, (fine_quarters(n, ich) + 3) / 4); }
 // slot buffers: the blocks' j sums, the workgroups' i sums and their carries, one after another
 struct FineSlots {
     size_t i_off, c_off, total;
 };
-FineSlots fine_slots(int64_t n, int wgs, int op, int prec)
+FineSlots fine_slots(int64_t n, int ich, int wgs, int op, int prec)
 {
     const size_t row = (size_t)fine_cols(op) * (is_f32(prec) ? sizeof(float) : sizeof(double));
     FineSlots f;
-    f.i_off = align256((size_t)fine_blocks(n) * fine_npad(n) * row);
-    f.c_off = f.i_off + align256((size_t)(wgs + fine_blocks(n)) * kFineRows * row);
+    f.i_off = align256((size_t)fine_blocks(n, ich) * fine_npad(n, ich) * row);
+    f.c_off = f.i_off + align256((size_t)(wgs + fine_blocks(n, ich)) * kFineWaves * ich * 64 * row);
     f.total = f.c_off + align256((size_t)wgs * 64 * row);
     return f;
 }
-size_t fine_partial_bytes(int64_t n, int op, int prec) { return fine_slots(n, fine_wgs_bound(n), op, prec).total; }
+size_t fine_partial_bytes(int64_t n, int ich, int op, int prec)
+{
+    return fine_slots(n, ich, fine_wgs_bound(n, ich), op, prec).total;
+}
+// what a workspace holds for the fine tiles: records and slots of either shape
+int64_t fine_records(int64_t n) { return std::max(fine_npad(n, kFineIch), fine_npad(n, kFineIch4)); }
+size_t fine_part(int64_t n, int op, int law, int prec)
+{
+    const size_t two = fine_partial_bytes(n, kFineIch, op, prec);
+    return fine_has4(op, law, prec) ? std::max(two, fine_partial_bytes(n, kFineIch4, op, prec)) : two;
+}
 
 bool sym_eligible(int api, int law, int prec)
 {
@@ -365,9 +384,10 @@ Cfg sanitize(Cfg c, int api, int law, int prec, int64_t npad)
             return c;
         }
         if (npad <= fine_max_n(api, law, prec)) {
-            c.block = kFineWaves * 64;                    // the fine tiles' one shape
-            c.ipl = kFineIch;
-            c.j_tile = kFineRows;
+            // the fine tiles' two shapes: blocks of four waves of two or four i chunks
+            c.block = kFineWaves * 64;
+            c.ipl = c.ipl == kFineIch4 && fine_has4(fine_op_of(api, law), law, prec) ? kFineIch4 : kFineIch;
+            c.j_tile = c.block * c.ipl;
             c.j_split = 1;
             return c;
         }
@@ -536,6 +556,7 @@ Cfg heuristic(int api, int law, int prec, int64_t n, int64_t nj, int64_t S, bool
         !(api == NBODY_API_BACKWARD && law == NBODY_LAW_LJC_LINEAR && (n < kFineAdjLjcMinN || n >= kSymAdjLjcMinN)) &&
         api != NBODY_API_JERK) {
         c.j_stage = kFineStage;
+        c.ipl = n >= kFineMin4 ? kFineIch4 : kFineIch;
         return sanitize(c, api, law, prec, npad);
     }
     const int smax = max_split_rows(n, nj);
@@ -690,6 +711,17 @@ Cfg choose(int api, const nbody_law *law, int64_t n, int64_t S, bool pot, int64_
     return heuristic(api, law->kind, law->precision, n, nj, S, pot);
 }
 
+// The configuration that runs for c, the rule's (ruled) or not, over a whole system of n: the fine
+// tiles in the place of the rule's coarser ones up to kFineForSym particles.
+Cfg run_cfg(const Cfg &c, bool ruled, int api, const nbody_law *law, int64_t n)
+{
+    if (!ruled || c.j_stage != kSymStage || n > kFineForSym || !sym_eligible(api, law->kind, law->precision)) return c;
+    Cfg f = c;
+    f.j_stage = kFineStage;
+    f.ipl = kFineIch4;                                // (two where four are not built)
+    return sanitize(f, api, law->kind, law->precision, round_up(n, 64));
+}
+
 // c, or the rule's one-sided configuration when c selects the symmetric tiles
 // (which evaluate whole systems only: not row subsets or exclusion lists)
 Cfg one_sided(const Cfg &c, int api, const nbody_law *law, int64_t n, int64_t nj, bool pot)
@@ -748,8 +780,8 @@ FwdWs fwd_layout(int api, const nbody_law *law, int64_t n)
     size_t part = (size_t)max_split(npad) * (size_t)npad * 4 * sizeof(double);
     if (sym) part = std::max(part, sym_max_partial_bytes(n));
     if (npad <= fine_max_n(api, law->kind, law->precision)) {
-        nrec = std::max(nrec, fine_npad(n));
-        part = std::max(part, fine_partial_bytes(n, FINE_FORCE, law->precision));
+        nrec = std::max(nrec, fine_records(n));
+        part = std::max(part, fine_part(n, FINE_FORCE, law->kind, law->precision));
     }
     // the row groups' leapfrog steps keep a second buffer of records
     if (npad <= rows_max_n(api, law->precision)) part = std::max(part, (size_t)npad * rec_bytes(law->kind, law->precision));
@@ -786,8 +818,8 @@ AdjWs adj_layout(const nbody_law *law, int64_t n)
     if (sym) part = std::max(part, sym_max_partial_bytes(n));
     if (ljs) part = std::max(part, symadj_ljc_partial_bytes(n));
     if (npad <= fine_max_n(NBODY_API_BACKWARD, law->kind, law->precision)) {
-        nrec = std::max(nrec, fine_npad(n));
-        part = std::max(part, fine_partial_bytes(n, fine_op_of(NBODY_API_BACKWARD, law->kind), law->precision));
+        nrec = std::max(nrec, fine_records(n));
+        part = std::max(part, fine_part(n, fine_op_of(NBODY_API_BACKWARD, law->kind), law->kind, law->precision));
     }
     size_t off = 0;
     w.rec_off = off;
@@ -822,8 +854,8 @@ JerkWs jerk_layout(int api, const nbody_law *law, int64_t n)
     size_t part = (size_t)max_split(npad) * (size_t)npad * 8 * sizeof(double);
     if (sym) part = std::max(part, symjerk_partial_bytes(n, symjerk_max_split(n)));
     if (npad <= fine_max_n(NBODY_API_JERK, law->kind, law->precision)) {
-        nrec = std::max(nrec, fine_npad(n));
-        part = std::max(part, fine_partial_bytes(n, FINE_JERK, law->precision));
+        nrec = std::max(nrec, fine_records(n));
+        part = std::max(part, fine_part(n, FINE_JERK, law->kind, law->precision));
     }
     size_t off = 0;
     w.rec_off = off;
@@ -1012,9 +1044,9 @@ Epilogue make_epi(const nbody_law *law, double *out_force, double *out_pot)
 // How the quarter sweeps of n particles are shared out: `per` quarters to each workgroup, m
 // workgroups per CU.  A CU's four SIMDs each run one wave of every workgroup on it, so the launch
 // takes about m * per quarters' time, over the rate a SIMD reaches with m waves to switch between.
-int fine_per(int64_t n)
+int fine_per(int64_t n, int ich)
 {
-    const int total = fine_begin(fine_blocks(n), fine_chunks(n));
+    const int total = fine_quarters(n, ich);
     constexpr double rate[] = {0.0, 0.60, 0.85, 0.96, 1.0};
     int best = 4;
     double cost = 1e300;
@@ -1030,8 +1062,8 @@ int fine_per(int64_t n)
     return best;
 }
 
-// A fine launch over the records and slot buffers of a workspace; `have` bytes of slots
-FineLaunch make_fine(int op, const nbody_law *law, int64_t n, bool pot, void *rec, void *slots)
+// A fine launch over the records and slot buffers of a workspace
+FineLaunch make_fine(int op, const nbody_law *law, int64_t n, int ich, bool pot, void *rec, void *slots)
 {
     FineLaunch a{};
     a.op = op;
@@ -1039,13 +1071,14 @@ FineLaunch make_fine(int op, const nbody_law *law, int64_t n, bool pot, void *re
     a.prec = law->precision;
     a.pot = pot ? 1 : 0;
     a.n = n;
+    a.ich = ich;
     a.nch = fine_chunks(n);
-    a.nb = fine_blocks(n);
-    a.per = fine_per(n);
-    a.nwg = (fine_begin(a.nb, a.nch) + a.per - 1) / a.per;
+    a.nb = fine_blocks(n, ich);
+    a.per = fine_per(n, ich);
+    a.nwg = (fine_quarters(n, ich) + a.per - 1) / a.per;
     a.eps2 = law->kind == NBODY_LAW_GRAVITY ? law->softening * law->softening : 0.0;
     for (int c = 0; c < 4; ++c) a.zeta[c] = law->kind == NBODY_LAW_LJC_SIGMOIDAL ? law->zeta[c] : 0.0;
-    const FineSlots f = fine_slots(n, a.nwg, op, law->precision);
+    const FineSlots f = fine_slots(n, ich, a.nwg, op, law->precision);
     a.rec = rec;
     a.jslot = slots;
     a.islot = (char *)slots + f.i_off;
@@ -1128,7 +1161,7 @@ int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const dou
     const bool sym = c.j_stage == kSymStage && rows == nullptr && nrows == n && excl.off == nullptr;
     const int blk = sym ? c.j_tile / 64 : 0;
     const bool fine = c.j_stage == kFineStage && rows == nullptr && nrows == n && excl.off == nullptr;
-    const int64_t npad = sym ? sym_npad(n, blk) : (fine ? fine_npad(n) : round_up(n, 64));
+    const int64_t npad = sym ? sym_npad(n, blk) : (fine ? fine_npad(n, c.ipl) : round_up(n, 64));
     char *base = (char *)ws;
     if (fine && c.block == kRowsBlock) return run_rows(law, pos, params, n, epi, pot, base, lay, s, pk_in, timed, packed, next);
     PackLaunch pk{};
@@ -1145,7 +1178,7 @@ int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const dou
     if (e != hipSuccess) return hip_fail(e, "pack");
 
     if (fine) {
-        FineLaunch a = make_fine(FINE_FORCE, law, n, pot, base + lay.rec_off, base + lay.part_off);
+        FineLaunch a = make_fine(FINE_FORCE, law, n, c.ipl, pot, base + lay.rec_off, base + lay.part_off);
         a.epi = epi;
         a.next = next;
         a.next.rec = base + lay.rec_off;
@@ -1169,6 +1202,9 @@ int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const dou
         a.partial = (float4 *)(base + lay.part_off);
         sym_share_range(a.nblk, share, n_shares, a.t0, a.count);
         a.epi = epi;
+        a.next = next;
+        a.next.rec = base + lay.rec_off;
+        a.next.rec_cols = (int)(rec_bytes(law->kind, law->precision) / sizeof(float));
         Timer t(s, timed);
         e = launch_sym(a, s);
         t.stop();
@@ -1234,7 +1270,7 @@ int run_jerk(const nbody_law *law, const Cfg &c, const JerkPackLaunch &pk_in, co
     if ((sym || fine) && (rows != nullptr || nrows != pk_in.n || !symjerk_ok(law->kind, law->precision) ||
                           pk_in.n > (fine ? fine_max_n(NBODY_API_JERK, law->kind, law->precision) : kSymJerkMaxN)))
         return fail(NBODY_EINVAL, "the symmetric jerk tiles evaluate whole systems of FP32 gravity only");
-    const int64_t npad = sym ? symjerk_npad(pk_in.n) : (fine ? fine_npad(pk_in.n) : round_up(pk_in.n, 64));
+    const int64_t npad = sym ? symjerk_npad(pk_in.n) : (fine ? fine_npad(pk_in.n, c.ipl) : round_up(pk_in.n, 64));
     char *base = (char *)ws;
     JerkPackLaunch pk = pk_in;
     pk.prec = law->precision;
@@ -1243,7 +1279,7 @@ int run_jerk(const nbody_law *law, const Cfg &c, const JerkPackLaunch &pk_in, co
     hipError_t e = launch_pack_jerk(pk, s);
     if (e != hipSuccess) return hip_fail(e, "jerk pack");
     if (fine) {
-        FineLaunch a = make_fine(FINE_JERK, law, pk_in.n, out_pot != nullptr, base + lay.rec_off, base + lay.part_off);
+        FineLaunch a = make_fine(FINE_JERK, law, pk_in.n, c.ipl, out_pot != nullptr, base + lay.rec_off, base + lay.part_off);
         a.out_acc = out_acc;
         a.out_jerk = out_jerk;
         a.out_pot = out_pot;
@@ -1337,7 +1373,7 @@ bool cfg_valid(const nbody_config *c)
            c->block % 64 == 0 && ipl_ok(c->i_per_lane) && c->j_tile >= 64 && c->j_tile % 64 == 0 &&
            c->j_tile <= (1 << 20) && c->j_split >= 1 && c->j_split <= kMaxSplit &&
            (c->j_stage == 0 || c->j_stage == 1 || c->j_stage == kSymStage ||
-            (c->j_stage == kFineStage && (rows || (c->i_per_lane == kFineIch && c->j_tile == kFineRows))));
+            (c->j_stage == kFineStage && (rows || ((c->i_per_lane == kFineIch || c->i_per_lane == kFineIch4) && c->j_tile == kFineWaves * 64 * c->i_per_lane))));
 }
 
 Cfg from_abi(const nbody_config *c)
@@ -1906,9 +1942,11 @@ int forces_impl(const double *pos, const double *params, int64_t n, const int64_
     rc = check_ws(ws, ws_bytes, lay.total);
     if (rc) return rc;
     const bool pot = out_potential != nullptr;
-    Cfg c = sanitize(forced ? *forced : choose(NBODY_API_FORCES, law, nrows, 1, pot, n), NBODY_API_FORCES,
+    bool ruled = false;
+    Cfg c = sanitize(forced ? *forced : choose(NBODY_API_FORCES, law, nrows, 1, pot, n, &ruled), NBODY_API_FORCES,
                      law->kind, law->precision, round_up(std::max(n, nrows), 64));
     if (rows || excl) c = one_sided(c, NBODY_API_FORCES, law, nrows, n, pot);
+    else c = run_cfg(c, ruled, NBODY_API_FORCES, law, n);
     const Cfg cs = with_excl(sanitize(c, NBODY_API_FORCES, law->kind, law->precision,
                                       round_up(std::max(n, nrows), 64)), excl != nullptr);
     return run_forward(law, cs, pos, params, n, rows, nrows, make_epi(law, out_force, out_potential),
@@ -2100,6 +2138,14 @@ std::vector<Cfg> candidate_set(int api, int law, int prec, int64_t n, bool pot)
                         }
         return out;
     }
+    if (npad <= fine_max_n(api, law, prec))    // the fine tiles' shapes
+        for (int ipl : {kFineIch, kFineIch4}) {
+            Cfg c;
+            c.j_stage = kFineStage;
+            c.ipl = ipl;
+            c = sanitize(c, api, law, prec, npad);
+            if (c.ipl == ipl) out.push_back(c);
+        }
     if (sym_eligible(api, law, prec) && npad <= kSymMaxN)
         for (int jt : {1024, 2048})            // the symmetric tiles, both block edges and shapes,
             for (int ipl : {2, 4})             // whole tiles or tiles in 2 or 4 j parts
@@ -2388,9 +2434,9 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
     if (c.j_stage == kFineStage) {
         // likewise the fine tiles' records and slots
         FwdWs lay{};
-        lay.part_off = align256((size_t)fine_npad(n) * rbytes);
+        lay.part_off = align256((size_t)fine_npad(n, c.ipl) * rbytes);
         lay.scratch_off = lay.total = kScratchBytes;
-        if (c.block == kRowsBlock || lay.part_off + fine_partial_bytes(n, FINE_FORCE, law->precision) <= kScratchBytes)
+        if (c.block == kRowsBlock || lay.part_off + fine_partial_bytes(n, c.ipl, FINE_FORCE, law->precision) <= kScratchBytes)
             return run_forward(law, c, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot,
                                base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
         c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
@@ -2456,8 +2502,10 @@ int backward_impl(const double *pos, const double *params, int64_t n, const nbod
     rc = check_ws(ws, ws_bytes, lay.total);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
-    Cfg c = sanitize(choose(NBODY_API_BACKWARD, law, n, 1, false), NBODY_API_BACKWARD, law->kind,
+    bool ruled;
+    Cfg c = sanitize(choose(NBODY_API_BACKWARD, law, n, 1, false, 0, &ruled), NBODY_API_BACKWARD, law->kind,
                      law->precision, round_up(n, 64));
+    if (!excl) c = run_cfg(c, ruled, NBODY_API_BACKWARD, law, n);
     if (excl && c.j_stage == kFineStage)              // the fine tiles take no exclusion lists
         c = sanitize(one_sided(c, NBODY_API_BACKWARD, law, n, n, false), NBODY_API_BACKWARD, law->kind,
                      law->precision, round_up(n, 64));
@@ -2468,7 +2516,7 @@ int backward_impl(const double *pos, const double *params, int64_t n, const nbod
         pk.law = law->kind;
         pk.prec = law->precision;
         pk.n = n;
-        pk.npad = fine_npad(n);
+        pk.npad = fine_npad(n, c.ipl);
         pk.pos = pos;
         pk.params = params;
         pk.g = grad_force;
@@ -2476,7 +2524,7 @@ int backward_impl(const double *pos, const double *params, int64_t n, const nbod
         pk.rec = base + lay.rec_off;
         hipError_t e = launch_pack_adjoint(pk, s);
         if (e != hipSuccess) return hip_fail(e, "adjoint pack");
-        FineLaunch a = make_fine(fine_op_of(NBODY_API_BACKWARD, law->kind), law, n, false, pk.rec, base + lay.part_off);
+        FineLaunch a = make_fine(fine_op_of(NBODY_API_BACKWARD, law->kind), law, n, c.ipl, false, pk.rec, base + lay.part_off);
         a.params = params;
         a.grad_pos = grad_pos;
         a.grad_params = grad_params;
@@ -2877,10 +2925,13 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
                            make_epi(law, (double *)(base + lay.scratch_off), out_potential), true, ws,
                            lay, s, nullptr);
     }
-    // The configurations of the steps: the last may ask for the potential.  With the fine tiles a
+    // The configurations of the steps: the last may ask for the potential.  With the pair tiles a
     // step's reduction also does the next step's kick and drift and moves its records along.
-    const Cfg mid = choose(NBODY_API_LEAPFROG, law, n, 1, false);
-    const Cfg end = out_potential ? choose(NBODY_API_LEAPFROG, law, n, 1, true) : mid;
+    bool rule_mid, rule_end;
+    Cfg mid = choose(NBODY_API_LEAPFROG, law, n, 1, false, 0, &rule_mid);
+    Cfg end = out_potential ? choose(NBODY_API_LEAPFROG, law, n, 1, true, 0, &rule_end) : mid;
+    end = run_cfg(end, out_potential ? rule_end : rule_mid, NBODY_API_LEAPFROG, law, n);
+    mid = run_cfg(mid, rule_mid, NBODY_API_LEAPFROG, law, n);
     bool packed = false, other = false;
     for (int32_t k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
@@ -2903,7 +2954,9 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
         other = packed && !other;
         if (packed && c.block == kRowsBlock) pk.rec = base + (other ? lay.part_off : lay.rec_off);
         const Cfg &after = k + 2 < nsteps ? mid : end;
-        if (!last && c.j_stage == kFineStage && after.j_stage == kFineStage && after.block == c.block) {
+        // (the records are padded to whole blocks, whose edges differ by shape)
+        if (!last && c.j_stage >= kSymStage && after.j_stage == c.j_stage &&
+            (c.j_stage == kSymStage || c.block != kRowsBlock ? after.j_tile == c.j_tile : after.block == c.block)) {
             next.on = 1;
             next.half_dt = 0.5 * dt;
             next.dt = dt;

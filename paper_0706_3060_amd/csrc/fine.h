@@ -13,31 +13,30 @@ namespace nbk {
 // without the potential).
 enum FineOp { FINE_FORCE = 0, FINE_HVP = 1, FINE_LJC_ADJ = 2, FINE_JERK = 3 };
 constexpr int kFineWaves = 4;                            // waves per workgroup
-constexpr int kFineIch = 2;                              // i chunks of 64 records per wave
-constexpr int kFineChunks = kFineWaves * kFineIch;       // chunks per block of rows
-constexpr int kFineRows = kFineChunks * 64;              // rows per block (512)
+constexpr int kFineIch = 2, kFineIch4 = 4;               // i chunks of 64 records per wave: 2 or 4
 constexpr int kFineMaxWgs = 2048;                        // workgroups of a launch, at most
 constexpr int64_t kFineMaxN = int64_t(1) << 18;
 
 // Columns of a slot row: the operator's sums rounded up to 4 or 8.
 __host__ __device__ inline int fine_cols(int op) { return op == FINE_LJC_ADJ || op == FINE_JERK ? 8 : 4; }
 
-// The work of n particles: nch chunks of 64 records, nb blocks of kFineRows rows.  Block b meets
-// chunks b kFineChunks .. nch - 1, one sweep of 64 steps each, cut into four quarters of 16 steps;
+// The work of n particles: nch chunks of 64 records, nb blocks of ch = kFineWaves ich chunks.  Block b
+// meets chunks b ch .. nch - 1, one sweep of 64 steps each, cut into four quarters of 16 steps;
 // the quarters of all blocks, block after block and chunk after chunk, form one line of
-// fine_begin(nb, nch) quarters that the workgroups share out in equal contiguous pieces.
-__host__ __device__ inline int fine_begin(int b, int nch) { return 4 * (b * nch - kFineChunks * (b * (b - 1) / 2)); }
+// fine_begin(nb, nch, ch) quarters that the workgroups share out in equal contiguous pieces.
+__host__ __device__ inline int fine_begin(int b, int nch, int ch) { return 4 * (b * nch - ch * (b * (b - 1) / 2)); }
 
 struct FineLaunch {
     int op, law, prec, pot;
     int64_t n;
+    int ich;                       // i chunks of a wave, 2 or 4
     int nch, nb;                   // chunks and blocks of the n particles
     int per, nwg;                  // quarters per workgroup (>= 4), workgroups
     double eps2;
     double zeta[4];
-    const void *rec;               // records, padded to nb * kFineRows
-    void *jslot;                   // [nb][nb kFineRows][cols] j sums of block b's sweeps
-    void *islot;                   // [nwg + nb][kFineRows][cols] i sums of workgroup w in block b: w + b
+    const void *rec;               // records, padded to whole blocks
+    void *jslot;                   // [nb][rows of nb blocks][cols] j sums of block b's sweeps
+    void *islot;                   // [nwg + nb][rows of a block][cols] i sums of workgroup w in block b: w + b
     void *carry;                   // [nwg][64][cols] j sums of a sweep that began in the workgroup before
     Epilogue epi;                  // FINE_FORCE
     StepNext next;
@@ -47,6 +46,7 @@ struct FineLaunch {
     double *out_acc, *out_jerk, *out_pot;
 };
 bool fine_supported(int op, int law, int prec);
+bool fine_has4(int op, int law, int prec);               // with four i chunks a wave too
 hipError_t launch_fine(const FineLaunch &a, hipStream_t s);
 hipError_t launch_fine_reduce(const FineLaunch &a, hipStream_t s);
 

@@ -2,9 +2,9 @@
 // particles (Newton's third law), in work units of 512 rows by 16 steps, for systems whose coarser
 // tiles would leave much of the chip idle and for FP64 pair arithmetic.
 //
-// Decomposition.  The rows form blocks of kFineChunks = 8 chunks of 64; a workgroup of four waves
-// holds one block in registers, two chunks a wave, and sweeps j chunks from the block's own onwards.
-// A sweep takes 64 steps: at step s lane l pairs its two i particles with particle j = l + s (mod
+// Decomposition.  The rows form blocks of 8 or 16 chunks of 64; a workgroup of four waves holds one
+// block in registers, two or four chunks a wave, and sweeps j chunks from the block's own onwards.
+// A sweep takes 64 steps: at step s lane l pairs its i particles with particle j = l + s (mod
 // 64) of the chunk, which is staged twice in LDS so that each lane reads its record at a constant
 // offset.  The j sums travel with their particle from lane to lane (most through the LDS crossbar,
 // the last on the VALU by a DPP rotation: the two units share the moves); after the sweep the four
@@ -278,24 +278,23 @@ __device__ __forceinline__ void move_on(int addr, T (&jv)[NC])
 
 // Steps s0 .. s1 - 1 of a sweep: the wave's i chunks before OWN against the chunk in `st`
 // symmetrically, i chunk OWN (when the wave has it: the chunk itself) one-sidedly.
-template <class Op, int OWN>
+template <class Op, int OWN, int I>
 __device__ __forceinline__ void fine_sweep(const float4 (&st)[kVecs<Op>][2 * kWave], int s0, int s1,
-                                           const typename Op::Rec (&iv)[kFineIch], const PairK<typename Op::T> &kc,
-                                           int addr, typename Op::T (&p)[kFineIch][Op::NC],
-                                           typename Op::T (&jv)[Op::NC])
+                                           const typename Op::Rec (&iv)[I], const PairK<typename Op::T> &kc,
+                                           int addr, typename Op::T (&p)[I][Op::NC], typename Op::T (&jv)[Op::NC])
 {
     using R = typename Op::Rec;
     const int lane = lane_id();
     R J = rec_from<Op>(&st[0][lane + s0], 2 * kWave);
     for (int s = s0; s < s1; s += kQuarter) {
         const float4 *at = &st[0][lane + s + 1];
-#pragma unroll 8
+#pragma unroll(16 / I)
         for (int u = 0; u < kQuarter; ++u) {
             // the next step's record, a step ahead (at most record 127 of the chunk staged twice)
             const R next = rec_from<Op>(at + u, 2 * kWave);
 #pragma unroll
             for (int k = 0; k < OWN; ++k) Op::template pair<true>(iv[k], J, kc, false, p[k], jv);
-            if constexpr (OWN < kFineIch) Op::template pair<false>(iv[OWN], J, kc, s + u == 0, p[OWN], jv);
+            if constexpr (OWN < I) Op::template pair<false>(iv[OWN], J, kc, s + u == 0, p[OWN], jv);
             if constexpr (OWN > 0) move_on<Op>(addr, jv);
             J = next;
         }
@@ -303,34 +302,35 @@ __device__ __forceinline__ void fine_sweep(const float4 (&st)[kVecs<Op>][2 * kWa
 }
 
 // the block of the quarter q: the last whose first quarter is at or before q
-__device__ __forceinline__ int fine_block(int q, int nb, int nch)
+__device__ __forceinline__ int fine_block(int q, int nb, int nch, int ch)
 {
     int lo = 0, hi = nb - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
-        if (fine_begin(mid, nch) <= q) lo = mid;
+        if (fine_begin(mid, nch, ch) <= q) lo = mid;
         else hi = mid - 1;
     }
     return lo;
 }
 
-// waves per SIMD the register allocation aims at
-template <class Op, int PREC> constexpr int fine_waves_per_eu()
+// waves per SIMD the register allocation aims at (FP64 with four i chunks holds 190 to 250 registers)
+template <class Op, int I> constexpr int fine_waves_per_eu()
 {
-    return sizeof(typename Op::T) == 8 || Op::NC >= 6 ? 3 : 4;
+    if (sizeof(typename Op::T) == 8) return I == 2 ? 3 : 2;
+    return Op::NC >= 6 ? 3 : 4;
 }
 
 }  // namespace
 
-template <class Op, int PREC>
-__global__ __launch_bounds__(kFineWaves * kWave) __attribute__((amdgpu_waves_per_eu(fine_waves_per_eu<Op, PREC>())))
+template <class Op, int PREC, int I>
+__global__ __launch_bounds__(kFineWaves * kWave) __attribute__((amdgpu_waves_per_eu(fine_waves_per_eu<Op, I>())))
 void k_fine(FineLaunch a)
 {
     using T = typename Op::T;
     using R = typename Op::Rec;
     constexpr int NC = Op::NC, NCP = NC > 4 ? 8 : 4, V = kVecs<Op>;
     constexpr int RV = Op::kCols * (int)sizeof(T) / 16;         // vectors from record to record
-    constexpr int I = kFineIch;
+    constexpr int kChunks = kFineWaves * I, kRows = kChunks * kWave;   // of a block
     __shared__ float4 st[2][V][2 * kWave];                      // the j chunk, staged twice, two buffers
     __shared__ T jr[2][kFineWaves][kWave][NCP];                 // the waves' j sums of a sweep, two buffers
     const int lane = lane_id();
@@ -338,14 +338,14 @@ void k_fine(FineLaunch a)
     const int nch = a.nch, nb = a.nb;
     // the workgroups reach the XCDs in turn: each XCD takes a contiguous run of pieces
     const int wg = (int)(blockIdx.x % kSymXcds) * (int)(gridDim.x / kSymXcds) + (int)(blockIdx.x / kSymXcds);
-    const int total = fine_begin(nb, nch);
+    const int total = fine_begin(nb, nch, kChunks);
     if (wg >= a.nwg || (int64_t)wg * a.per >= total) return;    // whole workgroup
     int q = wg * a.per;
     const int qe = q + a.per < total ? q + a.per : total;
-    int b = fine_block(q, nb, nch);
-    int jc = b * kFineChunks + (q - fine_begin(b, nch)) / 4;
+    int b = fine_block(q, nb, nch, kChunks);
+    int jc = b * kChunks + (q - fine_begin(b, nch, kChunks)) / 4;
     int s0 = (q % 4) * kQuarter;                                // fine_begin is a multiple of 4
-    const int64_t npad = (int64_t)nb * kFineRows;
+    const int64_t npad = (int64_t)nb * kRows;
     const float4 *__restrict__ rec4 = (const float4 *)a.rec;
     PairK<T> kc;
     kc.eps2 = (T)a.eps2;
@@ -363,7 +363,7 @@ void k_fine(FineLaunch a)
     auto load_block = [&]() {
 #pragma unroll
         for (int k = 0; k < I; ++k) {
-            iv[k] = rec_from<Op>(rec4 + ((int64_t)(b * kFineChunks + w * I + k) * kWave + lane) * RV, 1);
+            iv[k] = rec_from<Op>(rec4 + ((int64_t)(b * kChunks + w * I + k) * kWave + lane) * RV, 1);
 #pragma unroll
             for (int c = 0; c < NC; ++c) acc[k][c] = RunSum<PREC>{};
         }
@@ -395,12 +395,12 @@ void k_fine(FineLaunch a)
         // the sweep after this one
         const bool more = q < qe;
         const bool over = jc + 1 >= nch;                        // it begins the next block
-        const int jn = over ? (b + 1) * kFineChunks : jc + 1;
+        const int jn = over ? (b + 1) * kChunks : jc + 1;
         if (more) fetch(jn);
         T jv[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) jv[c] = T(0);
-        const int rel = jc - (b * kFineChunks + w * I);         // chunk jc against i chunk k of the wave: rel - k
+        const int rel = jc - (b * kChunks + w * I);         // chunk jc against i chunk k of the wave: rel - k
         if (rel >= 0) {
 #pragma unroll
             for (int k = 0; k < I; ++k)
@@ -409,8 +409,12 @@ void k_fine(FineLaunch a)
             // rel >= I: the chunk after all of the wave's i chunks; otherwise the chunk is i chunk rel,
             // and only the i chunks up to it meet it
             if (rel >= I) fine_sweep<Op, I>(st[buf], s0, s1, iv, kc, addr, p, jv);
+            else if (rel == 0) fine_sweep<Op, 0>(st[buf], s0, s1, iv, kc, addr, p, jv);
             else if (rel == 1) fine_sweep<Op, 1>(st[buf], s0, s1, iv, kc, addr, p, jv);
-            else fine_sweep<Op, 0>(st[buf], s0, s1, iv, kc, addr, p, jv);
+            else if constexpr (I > 2) {
+                if (rel == 2) fine_sweep<Op, 2>(st[buf], s0, s1, iv, kc, addr, p, jv);
+                else fine_sweep<Op, 3>(st[buf], s0, s1, iv, kc, addr, p, jv);
+            }
 #pragma unroll
             for (int k = 0; k < I; ++k)
 #pragma unroll
@@ -434,7 +438,7 @@ void k_fine(FineLaunch a)
             }
         }
         if (!more || over) {
-            T *dst = (T *)a.islot + (int64_t)(wg + b) * kFineRows * NCP;
+            T *dst = (T *)a.islot + (int64_t)(wg + b) * kRows * NCP;
 #pragma unroll
             for (int k = 0; k < I; ++k)
 #pragma unroll
@@ -456,7 +460,6 @@ void k_fine(FineLaunch a)
 // few rows and up to a hundred terms a row), each wave adding its own in order, and the waves' sums
 // merged in wave order, all in FP64 with compensation.  The operator's epilogue is separate for each
 // column.
-constexpr int kRedWaves = 8;
 template <typename T, int NCP>
 __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
 {
@@ -467,22 +470,23 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
     const int64_t r = t / NCP;
     const int c = (int)(t % NCP);
     const int jc = (int)(blockIdx.x / NCP);                     // 64 (row, column) pairs lie in one chunk
-    const int b = jc / kFineChunks, nch = a.nch, per = a.per;
-    const int64_t cols = (int64_t)a.nb * kFineRows * NCP;
+    const int ch = kFineWaves * a.ich, rows = ch * kWave;        // of a block
+    const int b = jc / ch, nch = a.nch, per = a.per;
+    const int64_t cols = (int64_t)a.nb * rows * NCP;
     const T *__restrict__ jslot = (const T *)a.jslot + t;
     const T *__restrict__ carry = (const T *)a.carry + (t - (int64_t)jc * kWave * NCP);
-    const T *__restrict__ islot = (const T *)a.islot + (t - (int64_t)b * kFineRows * NCP);
+    const T *__restrict__ islot = (const T *)a.islot + (t - (int64_t)b * rows * NCP);
     NSum v;
     for (int k = w; k <= b; k += kRedWaves) {
-        const int q = fine_begin(k, nch) + 4 * (jc - k * kFineChunks);
+        const int q = fine_begin(k, nch, ch) + 4 * (jc - k * ch);
         const int last = (q + 3) / per;
         v.add((double)jslot[k * cols]);
         if (q / per != last) v.add((double)carry[(int64_t)last * kWave * NCP]);
     }
-    const int w1 = (fine_begin(b + 1, nch) - 1) / per;
+    const int w1 = (fine_begin(b + 1, nch, ch) - 1) / per;
 #pragma unroll 4
-    for (int u = fine_begin(b, nch) / per + w; u <= w1; u += kRedWaves)
-        v.add((double)islot[(int64_t)(u + b) * kFineRows * NCP]);
+    for (int u = fine_begin(b, nch, ch) / per + w; u <= w1; u += kRedWaves)
+        v.add((double)islot[(int64_t)(u + b) * rows * NCP]);
     part[w][0][lane] = v.s;
     part[w][1][lane] = v.c;
     __syncthreads();
@@ -512,26 +516,36 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
     }
 }
 
-template <class Op, int PREC> static void fine_go(const FineLaunch &a, hipStream_t s)
+template <class Op, int PREC, bool FOUR> static void fine_go(const FineLaunch &a, hipStream_t s)
 {
-    const int grid = (a.nwg + kSymXcds - 1) / kSymXcds * kSymXcds;
-    hipLaunchKernelGGL((k_fine<Op, PREC>), dim3((unsigned)grid), dim3(kFineWaves * kWave), 0, s, a);
+    const dim3 grid((unsigned)((a.nwg + kSymXcds - 1) / kSymXcds * kSymXcds)), block(kFineWaves * kWave);
+    if constexpr (FOUR)
+        if (a.ich == kFineIch4) {
+            hipLaunchKernelGGL((k_fine<Op, PREC, kFineIch4>), grid, block, 0, s, a);
+            return;
+        }
+    hipLaunchKernelGGL((k_fine<Op, PREC, kFineIch>), grid, block, 0, s, a);
 }
-template <class Op> static void fine_go32(const FineLaunch &a, hipStream_t s)
+template <class Op, bool FOUR> static void fine_go32(const FineLaunch &a, hipStream_t s)
 {
-    if (a.prec == P_KAHAN) fine_go<Op, P_KAHAN>(a, s);
-    else fine_go<Op, P_FP64ACC>(a, s);
+    if (a.prec == P_KAHAN) fine_go<Op, P_KAHAN, FOUR>(a, s);
+    else fine_go<Op, P_FP64ACC, FOUR>(a, s);
 }
+template <template <typename, bool> class Op, bool POT, bool FOUR32> static void fine_go_law(const FineLaunch &a, hipStream_t s)
+{
+    if (a.prec == P_FP64) fine_go<Op<double, POT>, P_FP64, true>(a, s);
+    else fine_go32<Op<float, POT>, FOUR32>(a, s);
+}
+template <typename T, bool POT> using LjcLinOp = LjcOp<T, POT, LJC>;
+template <typename T, bool POT> using LjcConstOp = LjcOp<T, POT, LJC_CONST>;
+template <typename T, bool POT> using LjcSigOp = LjcOp<T, POT, LJC_SIG>;
 template <bool POT> static void fine_go_force(const FineLaunch &a, hipStream_t s)
 {
-    const bool d = a.prec == P_FP64;
     switch (a.law) {
-    case GRAVITY: d ? fine_go<GravOp<double, POT>, P_FP64>(a, s) : fine_go32<GravOp<float, POT>>(a, s); return;
-    case LJC: d ? fine_go<LjcOp<double, POT, LJC>, P_FP64>(a, s) : fine_go32<LjcOp<float, POT, LJC>>(a, s); return;
-    case LJC_CONST:
-        d ? fine_go<LjcOp<double, POT, LJC_CONST>, P_FP64>(a, s) : fine_go32<LjcOp<float, POT, LJC_CONST>>(a, s);
-        return;
-    default: d ? fine_go<LjcOp<double, POT, LJC_SIG>, P_FP64>(a, s) : fine_go32<LjcOp<float, POT, LJC_SIG>>(a, s);
+    case GRAVITY: return fine_go_law<GravOp, POT, true>(a, s);
+    case LJC: return fine_go_law<LjcLinOp, POT, false>(a, s);
+    case LJC_CONST: return fine_go_law<LjcConstOp, POT, false>(a, s);
+    default: return fine_go_law<LjcSigOp, POT, false>(a, s);
     }
 }
 
@@ -545,12 +559,22 @@ bool fine_supported(int op, int law, int prec)
     }
 }
 
+// FP64 forces and FP32 gravity's: elsewhere four chunks a wave cost more in balance than their moves
+// save (FP32, 30,011 particles: LJC(linear) with energies 317 us with two chunks against 342, gravity's
+// adjoint 314 against 319)
+bool fine_has4(int op, int law, int prec)
+{
+    return fine_supported(op, law, prec) && op == FINE_FORCE && (prec == P_FP64 || law == GRAVITY);
+}
+
 // a launch description that does not match the work of n particles is refused, never launched
 static bool fine_valid(const FineLaunch &a)
 {
     if (!fine_supported(a.op, a.law, a.prec) || a.n <= 0 || a.n > kFineMaxN) return false;
-    if (a.nch != (int)((a.n + kWave - 1) / kWave) || a.nb != (a.nch + kFineChunks - 1) / kFineChunks) return false;
-    const int total = fine_begin(a.nb, a.nch);
+    if (a.ich != kFineIch && !(a.ich == kFineIch4 && fine_has4(a.op, a.law, a.prec))) return false;
+    const int ch = kFineWaves * a.ich;
+    if (a.nch != (int)((a.n + kWave - 1) / kWave) || a.nb != (a.nch + ch - 1) / ch) return false;
+    const int total = fine_begin(a.nb, a.nch, ch);
     return a.per >= 4 && a.nwg == (total + a.per - 1) / a.per && a.nwg <= kFineMaxWgs && a.rec && a.jslot &&
            a.islot && a.carry;
 }
@@ -560,9 +584,9 @@ hipError_t launch_fine(const FineLaunch &a, hipStream_t s)
     if (!fine_valid(a)) return hipErrorInvalidValue;
     switch (a.op) {
     case FINE_FORCE: a.pot ? fine_go_force<true>(a, s) : fine_go_force<false>(a, s); break;
-    case FINE_HVP: fine_go32<HvpOp>(a, s); break;
-    case FINE_LJC_ADJ: fine_go32<LjcAdjOp>(a, s); break;
-    default: a.pot ? fine_go32<JerkOp<true>>(a, s) : fine_go32<JerkOp<false>>(a, s);
+    case FINE_HVP: fine_go32<HvpOp, false>(a, s); break;
+    case FINE_LJC_ADJ: fine_go32<LjcAdjOp, false>(a, s); break;
+    default: a.pot ? fine_go32<JerkOp<true>, false>(a, s) : fine_go32<JerkOp<false>, false>(a, s);
     }
     return hipGetLastError();
 }

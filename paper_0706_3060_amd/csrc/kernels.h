@@ -126,6 +126,7 @@ struct SymLaunch {
     float4 *partial;               // [split * nblk][npad] (x, y, z, potential) FP32 slot partials
     int64_t t0, count;             // order range of the launch's tiles (whole triangle: 0, sym_tiles)
     Epilogue epi;
+    StepNext next;
 };
 // Tile order of the symmetric launch.  The upper triangle (b1 <= b2) of the nblk x nblk block
 // grid is walked in strips of kSymStrip block rows, column by column inside a strip, so that

@@ -358,50 +358,77 @@ void k_sym(SymLaunch a)
     for (int ql = w; ql < jr; ql += WAVES) part_j[jrec0 + (int64_t)ql * kWave + lane] = jacc[ql * kWave + lane];
 }
 
-// Row r of block b: its slot partials in slot order (FP64, Neumaier), then the epilogue.  A
+// Row r of block b: its slot partials in FP64 (Neumaier), then the epilogue.  A
 // tile (b, k), k >= b, holds r on its i side: each of its parts wrote a partial for r (slots
 // split k .. split k + split - 1).  A tile (k, b), k < b, holds r on its j side: only the part
 // whose chunks include r's wrote one (slot split k + h_r).  When the launch covered one share
 // of the tiles, only the tiles in the share count (the test is the same for every row of a
-// workgroup: 256 rows lie in one block).
-__global__ __launch_bounds__(256) void k_sym_reduce(SymLaunch a)
+// workgroup: its rows lie in one block).
+//
+// A workgroup finishes 64 rows: wave w adds the slots of blocks w, w + 8, ... in order, four loads in
+// flight, and the waves' sums are merged in wave order.  One thread a row (the form before) left the
+// chip with too few loads in flight: 51 us at 65,536 particles in two parts (134 MB).
+constexpr int kRedWaves = 8;
+__global__ __launch_bounds__(kRedWaves * kWave) void k_sym_reduce(SymLaunch a)
 {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= a.n) return;
+    __shared__ double sums[kRedWaves][4][2][kWave];
+    const int lane = lane_id();
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = (int64_t)blockIdx.x * kWave + lane;      // always inside the padded rows
     NSum v[4];
     const float4 *__restrict__ part = a.partial;
     const bool whole = a.t0 == 0 && a.count == sym_tiles(a.nblk);
-    const int64_t b = r / ((int64_t)a.blk * kWave);
+    const int64_t b = (int64_t)blockIdx.x / a.blk;
     const int split = a.split;
-    const int hr = (int)((r % ((int64_t)a.blk * kWave)) / kWave) / (a.blk / split);   // r's part
-    for (int64_t k = 0; k < a.nblk; ++k) {
-        if (!whole) {
+    const int hr = (int)(blockIdx.x % a.blk) / (a.blk / split);   // the rows' part
+    // the slots in use, in order: block k < b has one, k >= b `split`
+    const int64_t used = b + (a.nblk - b) * split;
+    const auto slot = [&](int64_t u) { return u < b ? split * u + hr : split * b + (u - b); };
+    if (whole) {
+        int64_t u = w;
+        for (; u + 3 * kRedWaves < used; u += 4 * kRedWaves) {
+            float4 x[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[t] = part[slot(u + t * kRedWaves) * a.npad + r];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                v[0].add((double)x[t].x);
+                v[1].add((double)x[t].y);
+                v[2].add((double)x[t].z);
+                v[3].add((double)x[t].w);
+            }
+        }
+        for (; u < used; u += kRedWaves) {
+            const float4 x = part[slot(u) * a.npad + r];
+            v[0].add((double)x.x);
+            v[1].add((double)x.y);
+            v[2].add((double)x.z);
+            v[3].add((double)x.w);
+        }
+    } else {
+        for (int64_t u = w; u < used; u += kRedWaves) {
+            const int64_t k = u < b ? u : b + (u - b) / split;
             const int64_t t = b <= k ? sym_index_of(b, k, a.nblk) : sym_index_of(k, b, a.nblk);
             if (t < a.t0 || t >= a.t0 + a.count) continue;
-        }
-        for (int hh = k < b ? hr : 0; hh < (k < b ? hr + 1 : split); ++hh) {
-            const float4 x = part[(split * k + hh) * a.npad + r];
+            const float4 x = part[slot(u) * a.npad + r];
             v[0].add((double)x.x);
             v[1].add((double)x.y);
             v[2].add((double)x.z);
             v[3].add((double)x.w);
         }
     }
-    const Epilogue &e = a.epi;
-    double f0 = e.fscale * v[0].value(), f1 = e.fscale * v[1].value(), f2 = e.fscale * v[2].value();
-    if (e.kick) {
-        const double s = e.inv_mass ? e.inv_mass[r] : 1.0;
-        f0 *= s;
-        f1 *= s;
-        f2 *= s;
-        e.vel[3 * r] += e.half_dt * f0;
-        e.vel[3 * r + 1] += e.half_dt * f1;
-        e.vel[3 * r + 2] += e.half_dt * f2;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        sums[w][c][0][lane] = v[c].s;
+        sums[w][c][1][lane] = v[c].c;
     }
-    e.out_force[3 * r] = f0;
-    e.out_force[3 * r + 1] = f1;
-    e.out_force[3 * r + 2] = f2;
-    if (a.pot && e.out_pot) e.out_pot[r] = e.pscale * v[3].value();
+    __syncthreads();
+    // column w of the 64 rows, a wave each
+    if (w >= 4 || r >= a.n) return;
+    NSum x;
+#pragma unroll
+    for (int k = 0; k < kRedWaves; ++k) x.merge(sums[k][w][0][lane], sums[k][w][1][lane]);
+    finish_column<float>(a.epi, a.next, r, w, x.value(), a.pot != 0);
 }
 
 template <int OP, int WAVES, int ICH>
@@ -453,7 +480,7 @@ hipError_t launch_sym(const SymLaunch &a, hipStream_t s)
 hipError_t launch_sym_reduce(const SymLaunch &a, hipStream_t s)
 {
     if (a.n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sym_reduce, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_sym_reduce, dim3((unsigned)((a.n + kWave - 1) / kWave)), dim3(kRedWaves * kWave), 0, s, a);
     return hipGetLastError();
 }
 

@@ -17,7 +17,7 @@ from paper_0706_3060_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-FINE, ROWS = (256, 2, 512, 1, 3), (1024, 1, 1024, 1, 3)
+FINE, FINE4, ROWS = (256, 2, 512, 1, 3), (256, 4, 1024, 1, 3), (1024, 1, 1024, 1, 3)
 ROW_SIZES = [1, 2, 7, 65, 1000, 1023, 1025, 2051, 4096]
 SIZES = [1, 2, 63, 65, 511, 512, 513, 1025, 2049, 5003]
 ZC = (2.0e-4, -6.0e-3, 0.25, 0.4)
@@ -73,7 +73,8 @@ def seen(prec, a):
     return a if prec == "fp64" else W.round_to_f32(a)
 
 
-@pytest.mark.parametrize("cfg,n", [(FINE, n) for n in SIZES] + [(ROWS, n) for n in ROW_SIZES])
+@pytest.mark.parametrize("cfg,n", [(FINE, n) for n in SIZES] + [(FINE4, n) for n in SIZES[2:]]
+                         + [(ROWS, n) for n in ROW_SIZES])
 @pytest.mark.parametrize("prec", ["fp64", "fp32_kahan", "fp32_fp64acc"])
 def test_forces_of_every_law(fine, prec, cfg, n):
     nb = fine
@@ -89,7 +90,8 @@ def test_forces_of_every_law(fine, prec, cfg, n):
                  lambda: oracle.ljc_sigmoidal(xs, s.q, s.sigma, s.epsilon, ZC)))
     for law, pos, par, ref in runs:
         c = nb.get_config(nb.API_FORCES, n, law)
-        assert (c["block"], c["i_per_lane"], c["j_tile"], c["j_split"], c["j_stage"]) == cfg
+        four = cfg is not FINE4 or prec == "fp64" or law.kind == nb.GRAVITY      # where four i chunks are built
+        assert (c["block"], c["i_per_lane"], c["j_tile"], c["j_split"], c["j_stage"]) == (cfg if four else FINE)
         f, u = nb.forces(dev(pos), dev(par), law)
         f1, u1 = nb.forces(dev(pos), dev(par), law)
         f2, _ = nb.forces(dev(pos), dev(par), law, potential=False)
@@ -127,7 +129,7 @@ def test_adjoints_and_jerk(fine, prec, n):
     assert (np.abs(gt.cpu().numpy() - sums) <= 1e-3 * scale + 1e-300).all()
 
 
-@pytest.mark.parametrize("cfg", [FINE, ROWS])
+@pytest.mark.parametrize("cfg", [FINE, FINE4, ROWS])
 @pytest.mark.parametrize("law,prec", [("gravity", "fp64"), ("gravity", "fp32_kahan"), ("ljc", "fp32_fp64acc"),
                                       ("ljc", "fp64")])
 def test_steps_in_one_call_are_the_steps_one_by_one(fine, law, prec, cfg):
@@ -169,3 +171,36 @@ def test_rule_round_trip_and_allocation_free_call(nb):
             f, u = nb.forces(dev(x), dev(m), law)
             f1, u1 = nb.forces_noalloc(dev(x), dev(m), law)
             assert torch.equal(f, f1) and torch.equal(u, u1)
+
+
+@pytest.mark.parametrize("law,prec,shape", [("gravity", "fp32_kahan", FINE4), ("ljc", "fp32_fp64acc", FINE)])
+def test_the_fine_tiles_run_where_the_rule_reports_the_coarser_ones(nb, law, prec, shape):
+    """33,333 particles: the rule reports j_stage 2 and the fine tiles run, bit for bit as when forced; steps
+    in one call are the steps one by one there and above, where the coarser tiles run."""
+    for n in (33333, 66000):
+        if law == "gravity":
+            x, v, par = sphere(n, 31)
+            lw = nb.gravity(prec, softening=0.05)
+        else:
+            g = np.random.default_rng(5)
+            side = int(np.ceil(n ** (1 / 3)))
+            x = 3.2 * np.stack(np.unravel_index(np.arange(n), (side,) * 3), axis=1) + g.uniform(-0.3, 0.3, (n, 3))
+            par = np.stack([g.uniform(-0.5, 0.5, n), np.full(n, 3.2), np.full(n, 0.1)], axis=1)
+            v, lw = 1e-3 * g.standard_normal((n, 3)), nb.ljc_linear(prec)
+        X, P = dev(x), dev(par)
+        assert nb.get_config(nb.API_FORCES, n, lw)["j_stage"] == 2
+        f, u = nb.forces(X, P, lw)
+        if n <= 65536:
+            nb.set_config(nb.API_FORCES, *shape)
+            try:
+                f2, u2 = nb.forces(X, P, lw)
+            finally:
+                nb.clear_config(nb.API_FORCES)
+            assert torch.equal(f, f2) and torch.equal(u, u2)
+        out = []
+        for steps in ((3,), (1, 2)):
+            Y, V, A = X.clone(), dev(v), nb.forces(X, P, lw, potential=False)[0]
+            for k in steps:             # (above, the coarser tiles' shape differs with the potential)
+                w = nb.leapfrog(Y, V, A, P, lw, 1e-4, k, potential=k > 1)
+            out.append((Y, V, A, w))
+        assert all(torch.equal(a, b) for a, b in zip(*out))
