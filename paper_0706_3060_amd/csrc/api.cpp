@@ -1735,6 +1735,24 @@ bool bsym_takes(const nbody_law *law, const int64_t *offsets, int64_t S, bool ex
     return true;
 }
 
+// Parts of a tile's j chunks, a wave each.  A tile is 256 dependent steps, so few tiles leave the
+// SIMDs one or two waves and a long last one; parts give more waves, against a slot partial for
+// each that the reduction reads.  LJC linear, Kahan, random systems (whole call, one part -> parts):
+// 100 of 600-1,500 particles 122 -> 87 us with the potential and 84 -> 76 us without; 64 of
+// 500-5,000 296 -> 253 and 227 -> 219 us; 256 of 500-5,000 923 -> 888 us with the potential, but
+// 754 -> 765 us without.  So with the potential as many parts as the workspace's region holds, and
+// without it only until there are kBSymWantWaves waves.
+constexpr int64_t kBSymWantWaves = 8192;
+int bsym_split_of(const BatchPlan &plan, size_t part_bytes, bool pot)
+{
+    const int64_t tiles = (int64_t)plan.units.size() / 4;
+    int split = 1;
+    while (split < 4 && (pot || tiles * split < kBSymWantWaves) &&
+           (size_t)plan.n_slots * 4 * sizeof(float) * (size_t)(2 * split) <= part_bytes)
+        split *= 2;
+    return split;
+}
+
 // pack (systems padded to blocks of 256) + symmetric tiles + slot-ordered reduction
 int run_bsym(const nbody_law *law, const int64_t *offsets, int64_t S, const double *pos, const double *params,
              double *out_force, double *out_pot, void *ws, const BatWs &lay, hipStream_t s)
@@ -1781,6 +1799,7 @@ int run_bsym(const nbody_law *law, const int64_t *offsets, int64_t S, const doub
     for (int c = 0; c < 4; ++c) a.zeta[c] = law->kind == NBODY_LAW_LJC_SIGMOIDAL ? law->zeta[c] : 0.0;
     a.rec = base + lay.rec_off;
     a.partial = (float4 *)(base + lay.part_off);
+    a.split = bsym_split_of(plan, lay.part_bytes, a.pot);
     a.epi = make_epi(law, out_force, out_pot);
     Timer t(s);
     e = launch_bsym(a, s);

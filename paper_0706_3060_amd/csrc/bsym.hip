@@ -24,6 +24,14 @@
 // [nb_s][npad_s] (a diagonal tile adds both into slot b1), so every (slot,
 // row) is written exactly once; k_bsym_reduce adds a row's nb_s slots in slot
 // order in FP64 (Neumaier) and applies the epilogue.
+//
+// Parts.  A tile is 256 steps of four pairs for its wave, and an ensemble of a
+// few thousand tiles gives a SIMD one or two waves.  There the j chunks of a
+// tile are shared out to 2 or 4 waves: part h takes chunks h 4/split ..., its i
+// sums go to slot split b2 + h and the j sums of its chunks' rows to slot
+// split b1 + h (on the diagonal a part's own rows' j sums join its i sums, and
+// rows after its chunks have nothing to add).  100 systems of 600-1,500 with the potential:
+// the tiles 113 -> 76 us in four parts.  Reading the LDS record a step ahead cost 1 % and is not done.
 #include "allpairs.h"
 #include "kernels.h"
 
@@ -139,14 +147,16 @@ __device__ __forceinline__ void bs_sweep(const R *st, const BsI<LAW> (&iv)[kBSym
 // FP64 sums or the sigmoidal dielectric's longer sequence
 template <int LAW, int PREC> constexpr int bsym_waves_per_eu() { return PREC == P_KAHAN && LAW != LJC_SIG ? 4 : 3; }
 
-template <int LAW, int PREC, bool POT>
+template <int LAW, int PREC, bool POT, int SPLIT>
 __global__ __launch_bounds__(kBSymWaves * kWave) __attribute__((amdgpu_waves_per_eu(bsym_waves_per_eu<LAW, PREC>()))) void k_bsym(BSymLaunch a)
 {
     using R = typename RecOf<float, LAW>::type;
     const R *__restrict__ rec = (const R *)a.rec;
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t u = (int64_t)blockIdx.x * kBSymWaves + w;
+    constexpr int JR = kBSymChunks / SPLIT;                     // j chunks of a part
+    const int64_t u = ((int64_t)blockIdx.x * kBSymWaves + w) / SPLIT;
+    const int h = (int)(((int64_t)blockIdx.x * kBSymWaves + w) % SPLIT), q0 = h * JR;
     __shared__ R st_all[kBSymWaves][2 * kWave];                 // each wave's j chunk, staged twice
     __shared__ float4 jd_all[kBSymWaves][kBSymChunks][kWave];   // diagonal tiles: the j sums of block b1
     if (u >= a.n_units) return;                                 // whole wave; the kernel has no barriers
@@ -159,7 +169,10 @@ __global__ __launch_bounds__(kBSymWaves * kWave) __attribute__((amdgpu_waves_per
     if (b1 < 0 || b2 < b1 || b2 >= nb) return;                  // never index outside the tables
     const bool diag = b1 == b2;
     const int64_t irec0 = po + b1 * kBSymRecords, jrec0 = po + b2 * kBSymRecords;
-    float4 *slots = a.partial + a.systab[3 * s + 2];            // [nb][npad] of system s
+    float4 *slots = a.partial + a.systab[3 * s + 2] * SPLIT;    // [SPLIT nb][npad] of system s
+    // chunks of padding at the end of the system: nothing to do for a part that has only those
+    const int64_t ns = a.off[s + 1] - a.off[s];
+    if (SPLIT > 1 && b2 * kBSymRecords + q0 * kWave >= ns) return;
     R *st = st_all[w];
     PairK<float> kc;
     kc.eps2 = (float)a.eps2;
@@ -182,8 +195,10 @@ __global__ __launch_bounds__(kBSymWaves * kWave) __attribute__((amdgpu_waves_per
     static_assert(V == 1 || V == 2, "records of one or two 128-bit vectors");
     const float4 *__restrict__ rec4 = (const float4 *)a.rec;
     float4 *st4 = (float4 *)st;
-    float4 g0 = rec4[(jrec0 + lane) * V], g1 = V == 2 ? rec4[(jrec0 + lane) * V + 1] : float4{0, 0, 0, 0};
-    for (int q = 0; q < kBSymChunks; ++q) {
+    float4 g0 = rec4[(jrec0 + q0 * kWave + lane) * V];
+    float4 g1 = V == 2 ? rec4[(jrec0 + q0 * kWave + lane) * V + 1] : float4{0, 0, 0, 0};
+    for (int ql = 0; ql < JR; ++ql) {
+        const int q = q0 + ql;
         st4[lane * V] = g0;
         st4[(lane + kWave) * V] = g0;
         if (V == 2) {
@@ -191,7 +206,7 @@ __global__ __launch_bounds__(kBSymWaves * kWave) __attribute__((amdgpu_waves_per
             st4[(lane + kWave) * V + 1] = g1;
         }
         // the next chunk (the last round reloads its own, unused)
-        const int64_t qn = q + 1 < kBSymChunks ? q + 1 : q;
+        const int64_t qn = ql + 1 < JR ? q + 1 : q;
         g0 = rec4[(jrec0 + qn * kWave + lane) * V];
         if (V == 2) g1 = rec4[(jrec0 + qn * kWave + lane) * V + 1];
         __builtin_amdgcn_wave_barrier();
@@ -207,7 +222,7 @@ __global__ __launch_bounds__(kBSymWaves * kWave) __attribute__((amdgpu_waves_per
 #pragma unroll
             for (int c = 0; c < 4; ++c) acc[k][c].fold(p[k][c]);
         const float4 jq = float4{jv[0], jv[1], jv[2], POT ? jv[3] : 0.0f};
-        if (!diag) slots[b1 * npad + b2 * kBSymRecords + q * kWave + lane] = jq;   // slot b1, rows of b2
+        if (!diag) slots[(SPLIT * b1 + h) * npad + b2 * kBSymRecords + q * kWave + lane] = jq;   // rows of b2
         else jd_all[w][q][lane] = jq;
         __builtin_amdgcn_wave_barrier();                         // the slot is restaged next
     }
@@ -217,30 +232,44 @@ __global__ __launch_bounds__(kBSymWaves * kWave) __attribute__((amdgpu_waves_per
         float4 v = float4{(float)acc[k][0].value(), (float)acc[k][1].value(), (float)acc[k][2].value(),
                           POT ? (float)acc[k][3].value() : 0.0f};
         if (diag) {
-            const float4 t = jd_all[w][k][lane];
-            v = float4{v.x + t.x, v.y + t.y, v.z + t.z, v.w + t.w};
+            if (k >= q0 + JR) continue;                          // chunks after the part's
+            if (k >= q0) {
+                const float4 t = jd_all[w][k][lane];
+                v = float4{v.x + t.x, v.y + t.y, v.z + t.z, v.w + t.w};
+            }
         }
-        slots[b2 * npad + b1 * kBSymRecords + k * kWave + lane] = v;
+        slots[(SPLIT * b2 + h) * npad + b1 * kBSymRecords + k * kWave + lane] = v;
     }
 }
 
-// Row block red[blockIdx.x] = (s, rb) of 256 rows: each row adds its system's nb_s slots in
-// slot order (FP64, Neumaier) and applies the epilogue.
+// Row block red[blockIdx.x] = (s, rb) of 256 rows: each row adds its system's slots in slot order (FP64,
+// Neumaier) and applies the epilogue.  Slot by slot for block k: k < rb wrote one, the j sums of the
+// part with the row's chunk; k >= rb one for each part (on the diagonal from the row's part on, at
+// the end of the system up to the last part with particles).
 __global__ __launch_bounds__(kBSymRecords) void k_bsym_reduce(BSymLaunch a)
 {
     const int64_t s = a.red[2 * blockIdx.x], rb = a.red[2 * blockIdx.x + 1];
     const int64_t l = rb * kBSymRecords + threadIdx.x;
-    const int64_t o = a.off[s];
-    if (l >= a.off[s + 1] - o) return;
+    const int64_t o = a.off[s], ns = a.off[s + 1] - o;
+    if (l >= ns) return;
     const int64_t npad = a.poff[s + 1] - a.poff[s];
     const int64_t nb = npad / kBSymRecords;
-    const float4 *__restrict__ slots = a.partial + a.systab[3 * s + 2] + l;
+    const int split = a.split;
+    const int part = (int)(threadIdx.x / kWave) / (kBSymChunks / split);         // the row's
+    // parts of the last block's tiles that hold particles
+    const int64_t rest = (ns - (nb - 1) * kBSymRecords + kWave - 1) / kWave;     // its chunks
+    const int last = (int)((rest + kBSymChunks / split - 1) / (kBSymChunks / split));
+    const float4 *__restrict__ slots = a.partial + a.systab[3 * s + 2] * split + l;
+    // the slots in use, in order: rb of the blocks before, then from split rb + part on
+    const int64_t first = split * rb + part, end = split * (nb - 1) + last;
+    const int64_t used = rb + (end - first);
+    const auto at = [&](int64_t u) { return u < rb ? split * u + part : first + (u - rb); };
     NSum v[4];
     int64_t k = 0;
-    for (; k + 4 <= nb; k += 4) {            // four slots' loads in flight before their sums
+    for (; k + 4 <= used; k += 4) {          // four slots' loads in flight before their sums
         float4 x[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = slots[(k + t) * npad];
+        for (int t = 0; t < 4; ++t) x[t] = slots[at(k + t) * npad];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             v[0].add((double)x[t].x);
@@ -249,8 +278,8 @@ __global__ __launch_bounds__(kBSymRecords) void k_bsym_reduce(BSymLaunch a)
             v[3].add((double)x[t].w);
         }
     }
-    for (; k < nb; ++k) {
-        const float4 x = slots[k * npad];
+    for (; k < used; ++k) {
+        const float4 x = slots[at(k) * npad];
         v[0].add((double)x.x);
         v[1].add((double)x.y);
         v[2].add((double)x.z);
@@ -264,11 +293,18 @@ __global__ __launch_bounds__(kBSymRecords) void k_bsym_reduce(BSymLaunch a)
     if (a.pot && e.out_pot) e.out_pot[r] = e.pscale * v[3].value();
 }
 
+template <int LAW, int PREC, bool POT>
+static void bsym_split(const BSymLaunch &a, const dim3 &grid, const dim3 &block, hipStream_t s)
+{
+    if (a.split == 4) hipLaunchKernelGGL((k_bsym<LAW, PREC, POT, 4>), grid, block, 0, s, a);
+    else if (a.split == 2) hipLaunchKernelGGL((k_bsym<LAW, PREC, POT, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_bsym<LAW, PREC, POT, 1>), grid, block, 0, s, a);
+}
 template <int LAW, int PREC>
 static void bsym_go(const BSymLaunch &a, const dim3 &grid, const dim3 &block, hipStream_t s)
 {
-    if (a.pot) hipLaunchKernelGGL((k_bsym<LAW, PREC, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_bsym<LAW, PREC, false>), grid, block, 0, s, a);
+    if (a.pot) bsym_split<LAW, PREC, true>(a, grid, block, s);
+    else bsym_split<LAW, PREC, false>(a, grid, block, s);
 }
 
 bool bsym_supported(int law, int prec)
@@ -280,8 +316,8 @@ bool bsym_supported(int law, int prec)
 hipError_t launch_bsym(const BSymLaunch &a, hipStream_t s)
 {
     if (a.n_units <= 0) return hipSuccess;
-    if (!bsym_supported(a.law, a.prec)) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((a.n_units + kBSymWaves - 1) / kBSymWaves)), block(kBSymWaves * kWave);
+    if (!bsym_supported(a.law, a.prec) || (a.split != 1 && a.split != 2 && a.split != 4)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((a.n_units * a.split + kBSymWaves - 1) / kBSymWaves)), block(kBSymWaves * kWave);
     const bool kahan = a.prec == P_KAHAN;
     switch (a.law) {
     case GRAVITY: kahan ? bsym_go<GRAVITY, P_KAHAN>(a, grid, block, s) : bsym_go<GRAVITY, P_FP64ACC>(a, grid, block, s); break;

@@ -265,7 +265,8 @@ struct BSymLaunch {
     double eps2;
     double zeta[4];              // the sigmoidal dielectric's coefficients, as FwdLaunch::zeta
     const void *rec;             // FP32 records
-    float4 *partial;             // per system [nb][npad] (x, y, z, potential) FP32 slot partials
+    float4 *partial;             // per system [split nb][npad] (x, y, z, potential) FP32 slot partials
+    int split;                   // parts of a tile's j chunks, a wave each: 1, 2 or 4
     Epilogue epi;
 };
 bool bsym_supported(int law, int prec);
