@@ -75,7 +75,8 @@ struct BSymAdjLaunch {
     int64_t n_systems;
     double eps2, G, qscale;
     const void *rec;             // FP32 adjoint records
-    float4 *partial;             // per system [nb][npad][bsym_adj_sums(law) / 4 rounded up] FP32 slot sums
+    float4 *partial;             // per system [split nb][npad][bsym_adj_sums(law) / 4 rounded up] FP32 slot sums
+    int split;                   // parts of a tile's j chunks, a wave each: 1, 2 or 4 (one whole system: 1)
     const double *params;        // caller params (LJC: the epsilon gradient's scale)
     double *grad_pos;            // [n][3] or null
     double *grad_params;         // [n][3] or null (LJC)

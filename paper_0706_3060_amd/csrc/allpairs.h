@@ -394,4 +394,23 @@ __device__ __forceinline__ void j_range(const R *__restrict__ rec, int64_t jb, i
     j_range_masked<JS, Op, PREC, I>(rec, jb, je, j_tile, is, mask, kc, acc, p, wl);
 }
 
+// The slots that hold sums of a row (chunk c of block rb) in a system of ns particles whose symmetric
+// tiles come in `split` parts, in slot order: for a block before rb the part with the row's chunk; from
+// rb on every part (on the diagonal from the row's own on, in the last block those with particles).
+struct PartSlots {
+    int64_t rb, first, used;
+    int split, part;
+    __device__ __forceinline__ PartSlots(int64_t ns, int64_t nb, int64_t rb_, int chunk, int split_)
+        : rb(rb_), split(split_)
+    {
+        constexpr int chunks = kBSymRecords / kWave;
+        const int jr = chunks / split;                           // chunks of a part
+        part = chunk / jr;
+        const int64_t rest = (ns - (nb - 1) * kBSymRecords + kWave - 1) / kWave;     // the last block's
+        first = split * rb + part;
+        used = rb + (split * (nb - 1) + (rest + jr - 1) / jr - first);
+    }
+    __device__ __forceinline__ int64_t at(int64_t u) const { return u < rb ? split * u + part : first + (u - rb); }
+};
+
 }  // namespace nbk

@@ -1740,15 +1740,16 @@ bool bsym_takes(const nbody_law *law, const int64_t *offsets, int64_t S, bool ex
 // each that the reduction reads.  LJC linear, Kahan, random systems (whole call, one part -> parts):
 // 100 of 600-1,500 particles 122 -> 87 us with the potential and 84 -> 76 us without; 64 of
 // 500-5,000 296 -> 253 and 227 -> 219 us; 256 of 500-5,000 923 -> 888 us with the potential, but
-// 754 -> 765 us without.  So with the potential as many parts as the workspace's region holds, and
-// without it only until there are kBSymWantWaves waves.
+// 754 -> 765 us without.  The adjoint: 170 -> 143, 464 -> 436 and 1,592 -> 1,574 us.  So with the
+// potential and in the adjoint (`all`) as many parts as the workspace's region holds, and otherwise
+// only until there are kBSymWantWaves waves.
 constexpr int64_t kBSymWantWaves = 8192;
-int bsym_split_of(const BatchPlan &plan, size_t part_bytes, bool pot)
+int bsym_split_of(const BatchPlan &plan, size_t part_bytes, size_t row_bytes, bool all)
 {
     const int64_t tiles = (int64_t)plan.units.size() / 4;
     int split = 1;
-    while (split < 4 && (pot || tiles * split < kBSymWantWaves) &&
-           (size_t)plan.n_slots * 4 * sizeof(float) * (size_t)(2 * split) <= part_bytes)
+    while (split < 4 && (all || tiles * split < kBSymWantWaves) &&
+           (size_t)plan.n_slots * row_bytes * (size_t)(2 * split) <= part_bytes)
         split *= 2;
     return split;
 }
@@ -1799,7 +1800,7 @@ int run_bsym(const nbody_law *law, const int64_t *offsets, int64_t S, const doub
     for (int c = 0; c < 4; ++c) a.zeta[c] = law->kind == NBODY_LAW_LJC_SIGMOIDAL ? law->zeta[c] : 0.0;
     a.rec = base + lay.rec_off;
     a.partial = (float4 *)(base + lay.part_off);
-    a.split = bsym_split_of(plan, lay.part_bytes, a.pot);
+    a.split = bsym_split_of(plan, lay.part_bytes, 4 * sizeof(float), out_pot != nullptr);
     a.epi = make_epi(law, out_force, out_pot);
     Timer t(s);
     e = launch_bsym(a, s);
@@ -2578,6 +2579,7 @@ int backward_impl(const double *pos, const double *params, int64_t n, const nbod
         b.prec = law->precision;
         b.n_systems = 1;
         b.single_n = n;
+        b.split = 1;
         b.single_npad = spad;
         b.G = law->G;
         b.qscale = qscale_of(law);
@@ -2789,6 +2791,7 @@ int run_bsym_adj(const nbody_law *law, const int64_t *offsets, int64_t S, const 
     a.qscale = qscale_of(law);
     a.rec = base + lay.rec_off;
     a.partial = (float4 *)(base + lay.part_off);
+    a.split = bsym_split_of(plan, lay.part_bytes, (size_t)nv * 4 * sizeof(float), true);
     a.params = params;
     a.grad_pos = grad_pos;
     a.grad_params = grad_params;

@@ -243,9 +243,7 @@ __global__ __launch_bounds__(kBSymWaves * kWave) __attribute__((amdgpu_waves_per
 }
 
 // Row block red[blockIdx.x] = (s, rb) of 256 rows: each row adds its system's slots in slot order (FP64,
-// Neumaier) and applies the epilogue.  Slot by slot for block k: k < rb wrote one, the j sums of the
-// part with the row's chunk; k >= rb one for each part (on the diagonal from the row's part on, at
-// the end of the system up to the last part with particles).
+// Neumaier) and applies the epilogue.
 __global__ __launch_bounds__(kBSymRecords) void k_bsym_reduce(BSymLaunch a)
 {
     const int64_t s = a.red[2 * blockIdx.x], rb = a.red[2 * blockIdx.x + 1];
@@ -254,22 +252,14 @@ __global__ __launch_bounds__(kBSymRecords) void k_bsym_reduce(BSymLaunch a)
     if (l >= ns) return;
     const int64_t npad = a.poff[s + 1] - a.poff[s];
     const int64_t nb = npad / kBSymRecords;
-    const int split = a.split;
-    const int part = (int)(threadIdx.x / kWave) / (kBSymChunks / split);         // the row's
-    // parts of the last block's tiles that hold particles
-    const int64_t rest = (ns - (nb - 1) * kBSymRecords + kWave - 1) / kWave;     // its chunks
-    const int last = (int)((rest + kBSymChunks / split - 1) / (kBSymChunks / split));
-    const float4 *__restrict__ slots = a.partial + a.systab[3 * s + 2] * split + l;
-    // the slots in use, in order: rb of the blocks before, then from split rb + part on
-    const int64_t first = split * rb + part, end = split * (nb - 1) + last;
-    const int64_t used = rb + (end - first);
-    const auto at = [&](int64_t u) { return u < rb ? split * u + part : first + (u - rb); };
+    const PartSlots in(ns, nb, rb, (int)(threadIdx.x / kWave), a.split);
+    const float4 *__restrict__ slots = a.partial + a.systab[3 * s + 2] * a.split + l;
     NSum v[4];
     int64_t k = 0;
-    for (; k + 4 <= used; k += 4) {          // four slots' loads in flight before their sums
+    for (; k + 4 <= in.used; k += 4) {          // four slots' loads in flight before their sums
         float4 x[4];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) x[t] = slots[at(k + t) * npad];
+        for (int t = 0; t < 4; ++t) x[t] = slots[in.at(k + t) * npad];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             v[0].add((double)x[t].x);
@@ -278,8 +268,8 @@ __global__ __launch_bounds__(kBSymRecords) void k_bsym_reduce(BSymLaunch a)
             v[3].add((double)x[t].w);
         }
     }
-    for (; k < used; ++k) {
-        const float4 x = slots[at(k) * npad];
+    for (; k < in.used; ++k) {
+        const float4 x = slots[in.at(k) * npad];
         v[0].add((double)x.x);
         v[1].add((double)x.y);
         v[2].add((double)x.z);

@@ -27,7 +27,8 @@
 // one FP32 partial of each sum per row of b1 into slot b2 and one per row of b2
 // into slot b1 of system s's slots (a diagonal tile adds both into slot b1);
 // k_bsym_adj_reduce adds a row's slots in slot order in FP64 (Neumaier) and
-// writes the gradients.
+// writes the gradients.  The j chunks of an ensemble's tiles come in up to four
+// parts, a wave and a slot each, as the batched forward's do.
 #include "allpairs.h"
 #include "kernels.h"
 #include "adjoint.h"
@@ -181,7 +182,7 @@ template <int LAW, int PREC> constexpr int ba_waves_per_eu() { return LAW == GRA
 
 }  // namespace
 
-template <int LAW, int PREC>
+template <int LAW, int PREC, int SPLIT>
 __global__ __launch_bounds__(kWaves * kWave) __attribute__((amdgpu_waves_per_eu(ba_waves_per_eu<LAW, PREC>())))
 void k_bsym_adj(BSymAdjLaunch a)
 {
@@ -191,10 +192,12 @@ void k_bsym_adj(BSymAdjLaunch a)
     const int lane = lane_id();
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     __shared__ R st_all[kWaves][2 * kWave];                      // each wave's j chunk, staged twice
-    __shared__ float jd_all[kWaves][kChunks][NS][kWave];         // the j sums of block b2, per wave
+    constexpr int JR = kChunks / SPLIT;                          // j chunks of a part
+    __shared__ float jd_all[kWaves][JR][NS][kWave];              // the j sums of the part's chunks, per wave
     int64_t b1, b2, po, npad, slot0;
-    if (a.units) {
-        const int64_t u = (int64_t)blockIdx.x * kWaves + w;
+    const int h = SPLIT > 1 ? w % SPLIT : 0, q0 = h * JR;        // kWaves is a multiple of SPLIT
+    if (SPLIT > 1 || a.units) {
+        const int64_t u = ((int64_t)blockIdx.x * kWaves + w) / SPLIT;
         if (u >= a.n_units) return;                              // whole wave; the kernel has no barriers
         const int32_t *un = a.units + 4 * u;
         const int64_t s = un[0];
@@ -203,7 +206,9 @@ void k_bsym_adj(BSymAdjLaunch a)
         if (s < 0 || s >= a.n_systems) return;
         po = a.poff[s];
         npad = a.poff[s + 1] - po;
-        slot0 = a.systab[3 * s + 2];
+        slot0 = a.systab[3 * s + 2] * SPLIT;
+        // a part that holds only padding, at the end of the system
+        if (SPLIT > 1 && b2 * kBSymRecords + q0 * kWave >= a.off[s + 1] - a.off[s]) return;
     } else {
         // one system: the workgroups reach the XCDs in turn, so each XCD is given a contiguous
         // run of workgroups, four consecutive tiles of the strip order each
@@ -220,7 +225,7 @@ void k_bsym_adj(BSymAdjLaunch a)
     if (b1 < 0 || b2 < b1 || b2 >= nb) return;                   // never index outside the tables
     const bool diag = b1 == b2;
     const int64_t irec0 = po + b1 * kBSymRecords, jrec0 = po + b2 * kBSymRecords;
-    float4 *slots = a.partial + slot0 * NV;                      // [nb][npad][NV] of the system
+    float4 *slots = a.partial + slot0 * NV;                      // [SPLIT nb][npad][NV] of the system
     R *st = st_all[w];
     float(*jd)[NS][kWave] = jd_all[w];
     const float eps2 = (float)a.eps2;
@@ -228,7 +233,7 @@ void k_bsym_adj(BSymAdjLaunch a)
     const float4 *__restrict__ rec4 = (const float4 *)a.rec;
     float4 *st4 = (float4 *)st;
 #pragma unroll
-    for (int q = 0; q < kChunks; ++q)
+    for (int q = 0; q < JR; ++q)
 #pragma unroll
         for (int c = 0; c < NS; ++c) jd[q][c][lane] = 0.0f;
 
@@ -243,10 +248,11 @@ void k_bsym_adj(BSymAdjLaunch a)
         RunSum<PREC> acc[ICH][NS];
         float p[ICH][NS];
         // the next chunk's record of this lane, loaded a chunk ahead as 128-bit vectors
-        int64_t rj = (jrec0 + lane) * RS;
+        int64_t rj = (jrec0 + q0 * kWave + lane) * RS;
         float4 g0 = rec4[rj], g1 = rec4[rj + 1], g2 = V == 3 ? rec4[rj + 2] : float4{0, 0, 0, 0};
-        for (int q = 0; q < kChunks; ++q) {
-            const int qn = q + 1 < kChunks ? q + 1 : q;          // the last chunk reloads itself
+        for (int ql = 0; ql < JR; ++ql) {
+            const int q = q0 + ql;
+            const int qn = ql + 1 < JR ? q + 1 : q;              // the last chunk reloads itself
             if (diag && q < k0) {                                // no pair of these i chunks with q
                 rj = (jrec0 + (int64_t)qn * kWave + lane) * RS;
                 g0 = rec4[rj];
@@ -273,11 +279,11 @@ void k_bsym_adj(BSymAdjLaunch a)
                 for (int c = 0; c < NS; ++c) acc[kk][c].begin(p[kk][c]);
             float jv[NS];
 #pragma unroll
-            for (int c = 0; c < NS; ++c) jv[c] = jd[q][c][lane];
+            for (int c = 0; c < NS; ++c) jv[c] = jd[ql][c][lane];
             if (!diag) ba_sweep<LAW, false>(st, iv, eps2, q, k0, bp_addr, p, jv);
             else ba_sweep<LAW, true>(st, iv, eps2, q, k0, bp_addr, p, jv);
 #pragma unroll
-            for (int c = 0; c < NS; ++c) jd[q][c][lane] = jv[c];
+            for (int c = 0; c < NS; ++c) jd[ql][c][lane] = jv[c];
 #pragma unroll
             for (int kk = 0; kk < ICH; ++kk)
 #pragma unroll
@@ -289,12 +295,14 @@ void k_bsym_adj(BSymAdjLaunch a)
 #pragma unroll
         for (int kk = 0; kk < ICH; ++kk) {
             const int c = k0 + kk;
+            if (diag && c >= q0 + JR) continue;                  // chunks after the part's
+            const bool own = diag && c >= q0;
             float v[4 * NV];
 #pragma unroll
             for (int m = 0; m < 4 * NV; ++m) v[m] = 0.0f;
 #pragma unroll
-            for (int m = 0; m < NS; ++m) v[m] = (float)acc[kk][m].value() + (diag ? jd[c][m][lane] : 0.0f);
-            float4 *dst = slots + (b2 * npad + b1 * kBSymRecords + c * kWave + lane) * NV;
+            for (int m = 0; m < NS; ++m) v[m] = (float)acc[kk][m].value() + (own ? jd[c - q0][m][lane] : 0.0f);
+            float4 *dst = slots + ((SPLIT * b2 + h) * npad + b1 * kBSymRecords + c * kWave + lane) * NV;
 #pragma unroll
             for (int j = 0; j < NV; ++j) dst[j] = float4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]};
         }
@@ -302,11 +310,11 @@ void k_bsym_adj(BSymAdjLaunch a)
     // j sums: slot b1 of the rows of block b2
     if (!diag) {
 #pragma unroll
-        for (int q = 0; q < kChunks; ++q) {
+        for (int q = 0; q < JR; ++q) {
             float v[4 * NV];
 #pragma unroll
             for (int m = 0; m < 4 * NV; ++m) v[m] = m < NS ? jd[q][m][lane] : 0.0f;
-            float4 *dst = slots + (b1 * npad + b2 * kBSymRecords + q * kWave + lane) * NV;
+            float4 *dst = slots + ((SPLIT * b1 + h) * npad + b2 * kBSymRecords + (q0 + q) * kWave + lane) * NV;
 #pragma unroll
             for (int j = 0; j < NV; ++j) dst[j] = float4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]};
         }
@@ -323,15 +331,18 @@ __global__ __launch_bounds__(kBSymRecords) void k_bsym_adj_reduce(BSymAdjLaunch 
     const int64_t s = one ? 0 : a.red[2 * blockIdx.x], rb = one ? blockIdx.x : a.red[2 * blockIdx.x + 1];
     const int64_t l = rb * kBSymRecords + threadIdx.x;
     const int64_t o = one ? 0 : a.off[s];
-    if (l >= (one ? a.single_n : a.off[s + 1] - o)) return;
+    const int64_t ns = one ? a.single_n : a.off[s + 1] - o;
+    if (l >= ns) return;
     const int64_t npad = one ? a.single_npad : a.poff[s + 1] - a.poff[s];
     const int64_t nb = npad / kBSymRecords;
-    const float4 *__restrict__ slots = a.partial + ((one ? 0 : a.systab[3 * s + 2]) + l) * NV;
+    const PartSlots in(ns, nb, rb, (int)(threadIdx.x / kWave), a.split);
+    const float4 *__restrict__ slots = a.partial + ((one ? 0 : a.systab[3 * s + 2] * a.split) + l) * NV;
     NSum v[NS];
-    for (int64_t k = 0; k < nb; ++k) {
+#pragma unroll 4
+    for (int64_t k = 0; k < in.used; ++k) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
-            const float4 x = slots[k * npad * NV + j];
+            const float4 x = slots[in.at(k) * npad * NV + j];
             const float xs[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
             for (int m = 0; m < 4; ++m)
@@ -362,13 +373,22 @@ bool bsym_adj_supported(int law, int prec)
 
 int bsym_adj_sums(int law) { return law == GRAVITY ? BaShape<GRAVITY>::NS : BaShape<LJC>::NS; }
 
+static bool parts_ok(const BSymAdjLaunch &a) { return a.split == 1 || (a.units && (a.split == 2 || a.split == 4)); }
+template <int LAW, int PREC>
+static void bsym_adj_go(const BSymAdjLaunch &a, const dim3 &grid, const dim3 &block, hipStream_t s)
+{
+    if (a.split == 4) hipLaunchKernelGGL((k_bsym_adj<LAW, PREC, 4>), grid, block, 0, s, a);
+    else if (a.split == 2) hipLaunchKernelGGL((k_bsym_adj<LAW, PREC, 2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_bsym_adj<LAW, PREC, 1>), grid, block, 0, s, a);
+}
+
 hipError_t launch_bsym_adj(const BSymAdjLaunch &a, hipStream_t s)
 {
-    if (!bsym_adj_supported(a.law, a.prec)) return hipErrorInvalidValue;
+    if (!bsym_adj_supported(a.law, a.prec) || !parts_ok(a)) return hipErrorInvalidValue;
     int64_t wgs;
     if (a.units) {
         if (a.n_units <= 0) return hipSuccess;
-        wgs = (a.n_units + kWaves - 1) / kWaves;
+        wgs = (a.n_units * a.split + kWaves - 1) / kWaves;
     } else {
         if (a.single_n <= 0) return hipSuccess;
         if (a.single_npad % kBSymRecords != 0 || a.single_n > a.single_npad || a.red) return hipErrorInvalidValue;
@@ -377,18 +397,18 @@ hipError_t launch_bsym_adj(const BSymAdjLaunch &a, hipStream_t s)
     const dim3 grid((unsigned)wgs), block(kWaves * kWave);
     const bool kahan = a.prec == P_KAHAN;
     if (a.law == GRAVITY) {
-        if (kahan) hipLaunchKernelGGL((k_bsym_adj<GRAVITY, P_KAHAN>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_bsym_adj<GRAVITY, P_FP64ACC>), grid, block, 0, s, a);
+        if (kahan) bsym_adj_go<GRAVITY, P_KAHAN>(a, grid, block, s);
+        else bsym_adj_go<GRAVITY, P_FP64ACC>(a, grid, block, s);
     } else {
-        if (kahan) hipLaunchKernelGGL((k_bsym_adj<LJC, P_KAHAN>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_bsym_adj<LJC, P_FP64ACC>), grid, block, 0, s, a);
+        if (kahan) bsym_adj_go<LJC, P_KAHAN>(a, grid, block, s);
+        else bsym_adj_go<LJC, P_FP64ACC>(a, grid, block, s);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_bsym_adj_reduce(const BSymAdjLaunch &a, hipStream_t s)
 {
-    if (!bsym_adj_supported(a.law, a.prec)) return hipErrorInvalidValue;
+    if (!bsym_adj_supported(a.law, a.prec) || (a.split != 1 && (!a.red || (a.split != 2 && a.split != 4)))) return hipErrorInvalidValue;
     const int64_t blocks = a.red ? a.n_red : (a.single_n + kBSymRecords - 1) / kBSymRecords;
     if (blocks <= 0) return hipSuccess;
     if (!a.red && (a.units || a.single_npad % kBSymRecords != 0 || a.single_n > a.single_npad))
