@@ -36,8 +36,10 @@
  * the default for the forces from N = 32,768 to 2,097,152) evaluate each unordered pair once
  * and apply it to both particles through per-block partial sums that a
  * fixed-order reduction adds, without atomics; the batched entry point has
- * symmetric tiles of its own for gravity and LJC ensembles.  Either
- * way results are deterministic run to run.
+ * symmetric tiles of its own for gravity and LJC ensembles.  Fine pair tiles
+ * (j_stage 3) do the same in smaller work units from about 2,048 particles,
+ * FP64 pair arithmetic included, and row groups finish the forces of smaller
+ * systems in one launch.  Either way results are deterministic run to run.
  *
  * Conventions shared by every entry point
  * ---------------------------------------
@@ -312,7 +314,8 @@ int nbody_forces_share(const double *pos, const double *params, int64_t n, const
  * every law with FP32 pair arithmetic and systems of at most
  * 8192 particles, symmetric tiles of 256 x 256 records (each unordered pair
  * of a system evaluated once, per-system FP32 slot partials added in a fixed
- * order in FP64).  The workspace covers both: for those laws it holds up to
+ * order in FP64; a tile's j records come in up to 4 parts as far as the slots
+ * fit).  The workspace covers both: for those laws it holds up to
  * 512 bytes of slot partials per particle (32 slots of 16 bytes). */
 int nbody_forces_batched(const int64_t *offsets, int64_t n_systems, const double *pos,
                          const double *params, const nbody_law *law, double *out_force,

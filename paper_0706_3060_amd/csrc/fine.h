@@ -1,4 +1,4 @@
-// Internal interface between the host runtime (api.cpp) and the fine pair tiles (fine.hip).
+// Internal interface between the host runtime (api.cpp) and the fine pair tiles (fine.inl).
 // Not part of the public ABI (include/nbody.h).
 #pragma once
 #include "kernels.h"
