@@ -730,6 +730,18 @@ Cfg one_sided(const Cfg &c, int api, const nbody_law *law, int64_t n, int64_t nj
     return heuristic(api, law->kind, law->precision, n, nj, 1, pot, false);
 }
 
+bool is_rows(const Cfg &c) { return c.j_stage == kFineStage && c.block == kRowsBlock; }
+
+// Whether a leapfrog step with configuration c may kick, drift and move the records along for a next
+// step with configuration `after`: both the row groups (whose two record buffers alternate), or both
+// the same tiles with records padded to the same block edge.  The fine tiles with four i chunks and
+// the row groups share j_stage 3 and j_tile 1024, so the kernel is compared before the edge.
+bool hands_over(const Cfg &c, const Cfg &after)
+{
+    if (c.j_stage < kSymStage || after.j_stage != c.j_stage || is_rows(after) != is_rows(c)) return false;
+    return is_rows(c) || after.j_tile == c.j_tile;
+}
+
 // ------------------------------------------------------------ measurement
 bool g_timing = false;
 struct TimedLaunch {
@@ -1163,7 +1175,7 @@ int run_forward(const nbody_law *law, const Cfg &c, const double *pos, const dou
     const bool fine = c.j_stage == kFineStage && rows == nullptr && nrows == n && excl.off == nullptr;
     const int64_t npad = sym ? sym_npad(n, blk) : (fine ? fine_npad(n, c.ipl) : round_up(n, 64));
     char *base = (char *)ws;
-    if (fine && c.block == kRowsBlock) return run_rows(law, pos, params, n, epi, pot, base, lay, s, pk_in, timed, packed, next);
+    if (fine && is_rows(c)) return run_rows(law, pos, params, n, epi, pot, base, lay, s, pk_in, timed, packed, next);
     PackLaunch pk{};
     if (pk_in) pk = *pk_in;
     pk.law = law->kind;
@@ -2456,7 +2468,7 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
         FwdWs lay{};
         lay.part_off = align256((size_t)fine_npad(n, c.ipl) * rbytes);
         lay.scratch_off = lay.total = kScratchBytes;
-        if (c.block == kRowsBlock || lay.part_off + fine_partial_bytes(n, c.ipl, FINE_FORCE, law->precision) <= kScratchBytes)
+        if (is_rows(c) || lay.part_off + fine_partial_bytes(n, c.ipl, FINE_FORCE, law->precision) <= kScratchBytes)
             return run_forward(law, c, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot,
                                base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
         c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
@@ -2973,12 +2985,9 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
         epi.inv_mass = inv_mass;
         StepNext next{};
         // the row groups alternate between two record buffers
-        other = packed && !other;
-        if (packed && c.block == kRowsBlock) pk.rec = base + (other ? lay.part_off : lay.rec_off);
-        const Cfg &after = k + 2 < nsteps ? mid : end;
-        // (the records are padded to whole blocks, whose edges differ by shape)
-        if (!last && c.j_stage >= kSymStage && after.j_stage == c.j_stage &&
-            (c.j_stage == kSymStage || c.block != kRowsBlock ? after.j_tile == c.j_tile : after.block == c.block)) {
+        other = packed && is_rows(c) && !other;
+        if (other) pk.rec = base + lay.part_off;
+        if (!last && hands_over(c, k + 2 < nsteps ? mid : end)) {
             next.on = 1;
             next.half_dt = 0.5 * dt;
             next.dt = dt;
