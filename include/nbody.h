@@ -266,7 +266,11 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
  * Section 3.4: forces on a subset of i against all j).  `ilist` [ni] device
  * int64 holds indices in [0, n) (repeats allowed); row k of the outputs is
  * the force and potential of particle ilist[k].  Outputs are [ni][3] and [ni].
- * Workspace: nbody_workspace_bytes(NBODY_API_FORCES, max(n, ni), 1, law). */
+ * Workspace: nbody_workspace_bytes(NBODY_API_FORCES, max(n, ni), 1, law); the
+ * pair tiles' slots in that size are not used here, and a workspace of 2,048
+ * bytes and a record (16 or 32 bytes for FP32, 32 or 64 for FP64; gravity or
+ * LJC) for each of max(n, ni) particles, rounded up to a multiple of 64, and
+ * 512 bytes more is accepted. */
 int nbody_forces_subset(const double *pos, const double *params, int64_t n, const int64_t *ilist,
                         int64_t ni, const nbody_law *law, double *out_force,
                         double *out_potential, void *ws, size_t ws_bytes, void *stream);
@@ -363,7 +367,8 @@ int nbody_forces_backward(const double *pos, const double *params, int64_t n,
 
 /* nbody_forces with exclusion lists (LJC laws; NBODY_ENOTSUP for gravity and
  * NBODY_FP32_PLAIN).  `excl` (host struct, device arrays) must be non-NULL.
- * Workspace: nbody_workspace_bytes(NBODY_API_FORCES, n, 1, law). */
+ * Workspace: nbody_workspace_bytes(NBODY_API_FORCES, n, 1, law), or the
+ * smaller one that nbody_forces_subset accepts. */
 int nbody_forces_excl(const double *pos, const double *params, int64_t n,
                       const nbody_exclusions *excl, const nbody_law *law, double *out_force,
                       double *out_potential, void *ws, size_t ws_bytes, void *stream);
@@ -523,8 +528,11 @@ int hermite_block_steps(double *pos, double *vel, double *acc, double *jerk, dou
  * 2), whose FP32 partial buffer holds one partial per row and block of 2048
  * records: about n^2 / 128 bytes (8.6 GB at n = 2^20); up to n = 262,144 it
  * covers blocks of 1024 records (n^2 / 64 bytes), and up to n = 131,072 tiles
- * in 4 j parts (n^2 / 16 bytes, 1.1 GB at n = 2^17).  Returns 0 when the
- * arguments are invalid. */
+ * in 4 j parts (n^2 / 16 bytes, 1.1 GB at n = 2^17).  For FP64 through the
+ * forces and leapfrog entry points, n <= 262,144, it covers the fine pair
+ * tiles (j_stage 3): about n^2 / 64 bytes and 35 MB above 32,768 particles
+ * (0.31 GB at n = 2^17, 1.1 GB at 2^18).  Returns 0 when the arguments are
+ * invalid. */
 size_t nbody_workspace_bytes(int32_t api, int64_t n_total, int64_t n_systems,
                              const nbody_law *law);
 

@@ -148,7 +148,7 @@ size_t symadj_ljc_partial_bytes(int64_t n)
 
 // The fine pair tiles (fine.inl, j_stage 3): every unordered pair of a whole system once, in work
 // units small enough to fill the chip between the smallest systems and the sizes of the coarser
-// tiles; and, for FP64 pair arithmetic, which has no coarser tiles, up to kFineMaxN (4 GiB of slots).
+// tiles; and, for FP64 pair arithmetic, which has no coarser tiles, up to kFineMaxN (1.2 GB of slots).
 // The rule's lines, per call against the one-sided kernels (us, FP32 + Kahan unless said): at 2,050
 // particles 18-22 against 21-26 for gravity, LJC(linear), the jerk and gravity's adjoint, FP64 22
 // against 23; at 8,192 gravity 29 against 39, LJC(linear) with energies 38 against 52, the jerk 48
@@ -165,6 +165,8 @@ constexpr int64_t kFineAdjLjcMinN = 2560;
 // 18,000, 425 against 397 at 30,011, 1,147 against 1,075 at 50,001, 7,973 against 7,273 at 131,072; FP32
 // without them 52 against 55 at 12,000, 94 against 91 at 18,000, 213 against 201 at 30,011).
 constexpr int64_t kFineMin4 = 20480;
+// Above this size only four chunks, where they are built: two take twice the slots and are slower.
+constexpr int64_t kFineMax2 = int64_t(1) << 15;
 // Where the rule says the coarser tiles (j_stage 2), the fine tiles still run up to this size: against
 // them per call (us) at 33,000 particles LJC(linear) with energies 385 against 451, gravity's adjoint
 // 380 against 447; at 65,536 gravity 871 against 889 (963 against 964 with potentials), LJC(linear)
@@ -216,7 +218,7 @@ FineSlots fine_slots(int64_t n, int ich, int wgs, int op, int prec)
 {
     const size_t row = (size_t)fine_cols(op) * (is_f32(prec) ? sizeof(float) : sizeof(double));
     FineSlots f;
-    f.i_off = align256((size_t)fine_blocks(n, ich) * fine_npad(n, ich) * row);
+    f.i_off = align256((size_t)fine_jslot_rows(fine_blocks(n, ich), kFineWaves * ich * 64) * row);
     f.c_off = f.i_off + align256((size_t)(wgs + fine_blocks(n, ich)) * kFineWaves * ich * 64 * row);
     f.total = f.c_off + align256((size_t)wgs * 64 * row);
     return f;
@@ -225,12 +227,15 @@ size_t fine_partial_bytes(int64_t n, int ich, int op, int prec)
 {
     return fine_slots(n, ich, fine_wgs_bound(n, ich), op, prec).total;
 }
-// what a workspace holds for the fine tiles: records and slots of either shape
+// what a workspace holds for the fine tiles: records and slots of the shapes that may run at this size
+bool fine_two(int64_t n, int op, int law, int prec) { return n <= kFineMax2 || !fine_has4(op, law, prec); }
 int64_t fine_records(int64_t n) { return std::max(fine_npad(n, kFineIch), fine_npad(n, kFineIch4)); }
 size_t fine_part(int64_t n, int op, int law, int prec)
 {
-    const size_t two = fine_partial_bytes(n, kFineIch, op, prec);
-    return fine_has4(op, law, prec) ? std::max(two, fine_partial_bytes(n, kFineIch4, op, prec)) : two;
+    size_t b = 0;
+    if (fine_two(n, op, law, prec)) b = fine_partial_bytes(n, kFineIch, op, prec);
+    if (fine_has4(op, law, prec)) b = std::max(b, fine_partial_bytes(n, kFineIch4, op, prec));
+    return b;
 }
 
 bool sym_eligible(int api, int law, int prec)
@@ -386,7 +391,9 @@ Cfg sanitize(Cfg c, int api, int law, int prec, int64_t npad)
         if (npad <= fine_max_n(api, law, prec)) {
             // the fine tiles' two shapes: blocks of four waves of two or four i chunks
             c.block = kFineWaves * 64;
-            c.ipl = c.ipl == kFineIch4 && fine_has4(fine_op_of(api, law), law, prec) ? kFineIch4 : kFineIch;
+            const int op = fine_op_of(api, law);
+            c.ipl = fine_has4(op, law, prec) && (c.ipl == kFineIch4 || !fine_two(npad, op, law, prec)) ? kFineIch4
+                                                                                                     : kFineIch;
             c.j_tile = c.block * c.ipl;
             c.j_split = 1;
             return c;
@@ -781,19 +788,21 @@ struct FwdWs {
     size_t rec_off, part_off, scratch_off, total;
 };
 
-FwdWs fwd_layout(int api, const nbody_law *law, int64_t n)
+// whole: a call over every row without exclusion lists, which may run the pair tiles (the others
+// need none of their slots)
+FwdWs fwd_layout(int api, const nbody_law *law, int64_t n, bool whole = true)
 {
     FwdWs w{};
     const int64_t npad = round_up(std::max<int64_t>(n, 1), 64);
-    const bool sym = sym_eligible(api, law->kind, law->precision) && n <= kSymMaxN;
+    const bool sym = whole && sym_eligible(api, law->kind, law->precision) && n <= kSymMaxN;
     // the symmetric tiles pad the records to whole blocks and keep one FP32 partial per
     // row and block; the one-sided split keeps [split][rows][4] FP64 partials
     int64_t nrec = sym ? sym_npad(n, 32) : npad;
     size_t part = (size_t)max_split(npad) * (size_t)npad * 4 * sizeof(double);
     if (sym) part = std::max(part, sym_max_partial_bytes(n));
-    if (npad <= fine_max_n(api, law->kind, law->precision)) {
+    if (whole && npad <= fine_max_n(api, law->kind, law->precision)) {
         nrec = std::max(nrec, fine_records(n));
-        part = std::max(part, fine_part(n, FINE_FORCE, law->kind, law->precision));
+        part = std::max(part, fine_part(npad, FINE_FORCE, law->kind, law->precision));
     }
     // the row groups' leapfrog steps keep a second buffer of records
     if (npad <= rows_max_n(api, law->precision)) part = std::max(part, (size_t)npad * rec_bytes(law->kind, law->precision));
@@ -831,7 +840,7 @@ AdjWs adj_layout(const nbody_law *law, int64_t n)
     if (ljs) part = std::max(part, symadj_ljc_partial_bytes(n));
     if (npad <= fine_max_n(NBODY_API_BACKWARD, law->kind, law->precision)) {
         nrec = std::max(nrec, fine_records(n));
-        part = std::max(part, fine_part(n, fine_op_of(NBODY_API_BACKWARD, law->kind), law->kind, law->precision));
+        part = std::max(part, fine_part(npad, fine_op_of(NBODY_API_BACKWARD, law->kind), law->kind, law->precision));
     }
     size_t off = 0;
     w.rec_off = off;
@@ -867,7 +876,7 @@ JerkWs jerk_layout(int api, const nbody_law *law, int64_t n)
     if (sym) part = std::max(part, symjerk_partial_bytes(n, symjerk_max_split(n)));
     if (npad <= fine_max_n(NBODY_API_JERK, law->kind, law->precision)) {
         nrec = std::max(nrec, fine_records(n));
-        part = std::max(part, fine_part(n, FINE_JERK, law->kind, law->precision));
+        part = std::max(part, fine_part(npad, FINE_JERK, law->kind, law->precision));
     }
     size_t off = 0;
     w.rec_off = off;
@@ -1970,7 +1979,7 @@ int forces_impl(const double *pos, const double *params, int64_t n, const int64_
     if (nrows == 0) return NBODY_OK;
     if (!pos || !params || !out_force) return fail(NBODY_EINVAL, "pos, params and out_force must be non-NULL");
     if (rows == nullptr && nrows != n) return fail(NBODY_EINVAL, "row count mismatch");
-    const FwdWs lay = fwd_layout(NBODY_API_FORCES, law, std::max(n, nrows));
+    const FwdWs lay = fwd_layout(NBODY_API_FORCES, law, std::max(n, nrows), rows == nullptr && excl == nullptr);
     rc = check_ws(ws, ws_bytes, lay.total);
     if (rc) return rc;
     const bool pot = out_potential != nullptr;

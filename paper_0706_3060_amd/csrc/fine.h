@@ -14,7 +14,7 @@ namespace nbk {
 enum FineOp { FINE_FORCE = 0, FINE_HVP = 1, FINE_LJC_ADJ = 2, FINE_JERK = 3 };
 constexpr int kFineWaves = 4;                            // waves per workgroup
 constexpr int kFineIch = 2, kFineIch4 = 4;               // i chunks of 64 records per wave: 2 or 4
-constexpr int kFineMaxWgs = 2048;                        // workgroups of a launch, at most
+constexpr int kFineMaxWgs = 1024;                        // workgroups of a launch, at most: four on each of 256 CUs
 constexpr int64_t kFineMaxN = int64_t(1) << 18;
 
 // Columns of a slot row: the operator's sums rounded up to 4 or 8.
@@ -26,6 +26,13 @@ __host__ __device__ inline int fine_cols(int op) { return op == FINE_LJC_ADJ || 
 // fine_begin(nb, nch, ch) quarters that the workgroups share out in equal contiguous pieces.
 __host__ __device__ inline int fine_begin(int b, int nch, int ch) { return 4 * (b * nch - ch * (b * (b - 1) / 2)); }
 
+// The j slots of the blocks follow one another, block b's from its own first row on (it meets no
+// row before): row r (of nb blocks of `rows`) of block b lies at slot row fine_jslot(b, nb, rows) + r, of
+// fine_jslot_rows(nb, rows) in all.
+// (At most 2^25.1 rows, 2^18 particles in blocks of 1,024.)
+__host__ __device__ inline int fine_jslot(int b, int nb, int rows) { return rows * (b * nb - b * (b + 1) / 2); }
+__host__ __device__ inline int fine_jslot_rows(int nb, int rows) { return rows * (nb * (nb + 1) / 2); }
+
 struct FineLaunch {
     int op, law, prec, pot;
     int64_t n;
@@ -35,7 +42,7 @@ struct FineLaunch {
     double eps2;
     double zeta[4];
     const void *rec;               // records, padded to whole blocks
-    void *jslot;                   // [nb][rows of nb blocks][cols] j sums of block b's sweeps
+    void *jslot;                   // [fine_jslot_rows][cols] j sums of the blocks' sweeps
     void *islot;                   // [nwg + nb][rows of a block][cols] i sums of workgroup w in block b: w + b
     void *carry;                   // [nwg][64][cols] j sums of a sweep that began in the workgroup before
     Epilogue epi;                  // FINE_FORCE

@@ -345,7 +345,6 @@ void k_fine(FineLaunch a)
     int b = fine_block(q, nb, nch, kChunks);
     int jc = b * kChunks + (q - fine_begin(b, nch, kChunks)) / 4;
     int s0 = (q % 4) * kQuarter;                                // fine_begin is a multiple of 4
-    const int64_t npad = (int64_t)nb * kRows;
     const float4 *__restrict__ rec4 = (const float4 *)a.rec;
     PairK<T> kc;
     kc.eps2 = (T)a.eps2;
@@ -428,7 +427,7 @@ void k_fine(FineLaunch a)
         // have all reached this barrier's predecessor.
         __syncthreads();
         {
-            T *dst = s0 == 0 ? (T *)a.jslot + ((int64_t)b * npad + (int64_t)jc * kWave) * NCP
+            T *dst = s0 == 0 ? (T *)a.jslot + (int64_t)(fine_jslot(b, nb, kRows) + jc * kWave) * NCP
                              : (T *)a.carry + (int64_t)wg * kWave * NCP;
             for (int e = threadIdx.x; e < kWave * NCP; e += kFineWaves * kWave) {
                 T v = (&jr[buf][0][0][0])[e];
@@ -472,15 +471,18 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
     const int jc = (int)(blockIdx.x / NCP);                     // 64 (row, column) pairs lie in one chunk
     const int ch = kFineWaves * a.ich, rows = ch * kWave;        // of a block
     const int b = jc / ch, nch = a.nch, per = a.per;
-    const int64_t cols = (int64_t)a.nb * rows * NCP;
     const T *__restrict__ jslot = (const T *)a.jslot + t;
     const T *__restrict__ carry = (const T *)a.carry + (t - (int64_t)jc * kWave * NCP);
     const T *__restrict__ islot = (const T *)a.islot + (t - (int64_t)b * rows * NCP);
     NSum v;
+    // fine_jslot(k), kRedWaves blocks a time
+    int at = fine_jslot(w, a.nb, rows), step = rows * kRedWaves * (2 * (a.nb - w) - kRedWaves - 1) / 2;
     for (int k = w; k <= b; k += kRedWaves) {
         const int q = fine_begin(k, nch, ch) + 4 * (jc - k * ch);
         const int last = (q + 3) / per;
-        v.add((double)jslot[k * cols]);
+        v.add((double)jslot[(int64_t)at * NCP]);
+        at += step;
+        step -= rows * kRedWaves * kRedWaves;
         if (q / per != last) v.add((double)carry[(int64_t)last * kWave * NCP]);
     }
     const int w1 = (fine_begin(b + 1, nch, ch) - 1) / per;
