@@ -210,13 +210,16 @@ int64_t fine_npad(int64_t n, int ich) { return (int64_t)fine_blocks(n, ich) * kF
 int fine_quarters(int64_t n, int ich) { return fine_begin(fine_blocks(n, ich), fine_chunks(n), kFineWaves * ich); }
 // most workgroups a launch over n particles has: four quarters of a sweep each at least
 int fine_wgs_bound(int64_t n, int ich) { return std::min(kFineMaxWgs, (fine_quarters(n, ich) + 3) / 4); }
+// FP32 pair arithmetic: FP64 slots where the one-sided kernels would run, whose j parts are FP64, and
+// FP32 slots from the coarser tiles' sizes on, as theirs are
+bool fine_wide(int64_t n, int prec) { return !is_f32(prec) || n < kSymMinN; }
 // slot buffers: the blocks' j sums, the workgroups' i sums and their carries, one after another
 struct FineSlots {
     size_t i_off, c_off, total;
 };
 FineSlots fine_slots(int64_t n, int ich, int wgs, int op, int prec)
 {
-    const size_t row = (size_t)fine_cols(op) * (is_f32(prec) ? sizeof(float) : sizeof(double));
+    const size_t row = (size_t)fine_cols(op) * (fine_wide(n, prec) ? sizeof(double) : sizeof(float));
     FineSlots f;
     f.i_off = align256((size_t)fine_jslot_rows(fine_blocks(n, ich), kFineWaves * ich * 64) * row);
     f.c_off = f.i_off + align256((size_t)(wgs + fine_blocks(n, ich)) * kFineWaves * ich * 64 * row);
@@ -228,12 +231,12 @@ size_t fine_partial_bytes(int64_t n, int ich, int op, int prec)
     return fine_slots(n, ich, fine_wgs_bound(n, ich), op, prec).total;
 }
 // what a workspace holds for the fine tiles: records and slots of the shapes that may run at this size
-bool fine_two(int64_t n, int op, int law, int prec) { return n <= kFineMax2 || !fine_has4(op, law, prec); }
+bool fine_two(int64_t npad, int op, int law, int prec) { return npad <= kFineMax2 || !fine_has4(op, law, prec); }
 int64_t fine_records(int64_t n) { return std::max(fine_npad(n, kFineIch), fine_npad(n, kFineIch4)); }
 size_t fine_part(int64_t n, int op, int law, int prec)
 {
     size_t b = 0;
-    if (fine_two(n, op, law, prec)) b = fine_partial_bytes(n, kFineIch, op, prec);
+    if (fine_two(round_up(n, 64), op, law, prec)) b = fine_partial_bytes(n, kFineIch, op, prec);
     if (fine_has4(op, law, prec)) b = std::max(b, fine_partial_bytes(n, kFineIch4, op, prec));
     return b;
 }
@@ -802,7 +805,7 @@ FwdWs fwd_layout(int api, const nbody_law *law, int64_t n, bool whole = true)
     if (sym) part = std::max(part, sym_max_partial_bytes(n));
     if (whole && npad <= fine_max_n(api, law->kind, law->precision)) {
         nrec = std::max(nrec, fine_records(n));
-        part = std::max(part, fine_part(npad, FINE_FORCE, law->kind, law->precision));
+        part = std::max(part, fine_part(n, FINE_FORCE, law->kind, law->precision));
     }
     // the row groups' leapfrog steps keep a second buffer of records
     if (npad <= rows_max_n(api, law->precision)) part = std::max(part, (size_t)npad * rec_bytes(law->kind, law->precision));
@@ -840,7 +843,7 @@ AdjWs adj_layout(const nbody_law *law, int64_t n)
     if (ljs) part = std::max(part, symadj_ljc_partial_bytes(n));
     if (npad <= fine_max_n(NBODY_API_BACKWARD, law->kind, law->precision)) {
         nrec = std::max(nrec, fine_records(n));
-        part = std::max(part, fine_part(npad, fine_op_of(NBODY_API_BACKWARD, law->kind), law->kind, law->precision));
+        part = std::max(part, fine_part(n, fine_op_of(NBODY_API_BACKWARD, law->kind), law->kind, law->precision));
     }
     size_t off = 0;
     w.rec_off = off;
@@ -876,7 +879,7 @@ JerkWs jerk_layout(int api, const nbody_law *law, int64_t n)
     if (sym) part = std::max(part, symjerk_partial_bytes(n, symjerk_max_split(n)));
     if (npad <= fine_max_n(NBODY_API_JERK, law->kind, law->precision)) {
         nrec = std::max(nrec, fine_records(n));
-        part = std::max(part, fine_part(npad, FINE_JERK, law->kind, law->precision));
+        part = std::max(part, fine_part(n, FINE_JERK, law->kind, law->precision));
     }
     size_t off = 0;
     w.rec_off = off;
@@ -1083,6 +1086,17 @@ int fine_per(int64_t n, int ich)
     return best;
 }
 
+int fine_wgs(int64_t n, int ich)
+{
+    const int per = fine_per(n, ich);
+    return (fine_quarters(n, ich) + per - 1) / per;
+}
+// slots of a launch on this device
+size_t fine_launch_bytes(int64_t n, int ich, int op, int prec)
+{
+    return fine_slots(n, ich, fine_wgs(n, ich), op, prec).total;
+}
+
 // A fine launch over the records and slot buffers of a workspace
 FineLaunch make_fine(int op, const nbody_law *law, int64_t n, int ich, bool pot, void *rec, void *slots)
 {
@@ -1096,9 +1110,10 @@ FineLaunch make_fine(int op, const nbody_law *law, int64_t n, int ich, bool pot,
     a.nch = fine_chunks(n);
     a.nb = fine_blocks(n, ich);
     a.per = fine_per(n, ich);
-    a.nwg = (fine_quarters(n, ich) + a.per - 1) / a.per;
+    a.nwg = fine_wgs(n, ich);
     a.eps2 = law->kind == NBODY_LAW_GRAVITY ? law->softening * law->softening : 0.0;
     for (int c = 0; c < 4; ++c) a.zeta[c] = law->kind == NBODY_LAW_LJC_SIGMOIDAL ? law->zeta[c] : 0.0;
+    a.wide = fine_wide(n, law->precision) ? 1 : 0;
     const FineSlots f = fine_slots(n, ich, a.nwg, op, law->precision);
     a.rec = rec;
     a.jslot = slots;
@@ -2477,7 +2492,7 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
         FwdWs lay{};
         lay.part_off = align256((size_t)fine_npad(n, c.ipl) * rbytes);
         lay.scratch_off = lay.total = kScratchBytes;
-        if (is_rows(c) || lay.part_off + fine_partial_bytes(n, c.ipl, FINE_FORCE, law->precision) <= kScratchBytes)
+        if (is_rows(c) || lay.part_off + fine_launch_bytes(n, c.ipl, FINE_FORCE, law->precision) <= kScratchBytes)
             return run_forward(law, c, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot,
                                base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
         c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,

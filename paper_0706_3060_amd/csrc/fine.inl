@@ -1,8 +1,8 @@
 // Fine pair tiles: every unordered pair {i, j} of one whole system once, its terms applied to both
-// particles (Newton's third law), in work units of 512 rows by 16 steps, for systems whose coarser
+// particles (Newton's third law), in work units of a block's rows by 16 steps, for systems whose coarser
 // tiles would leave much of the chip idle and for FP64 pair arithmetic.
 //
-// Decomposition.  The rows form blocks of 8 or 16 chunks of 64; a workgroup of four waves holds one
+// Decomposition.  The rows form blocks of 8 or 16 chunks of 64 (512 or 1,024 rows); a workgroup of four waves holds one
 // block in registers, two or four chunks a wave, and sweeps j chunks from the block's own onwards.
 // A sweep takes 64 steps: at step s lane l pairs its i particles with particle j = l + s (mod
 // 64) of the chunk, which is staged twice in LDS so that each lane reads its record at a constant
@@ -19,10 +19,13 @@
 // workgroup's carry row.  A piece that crosses into the next block writes the i sums of the block it
 // leaves and loads the next.
 //
-// Sums.  i sums: FP32 partials of a sweep (64 steps) folded into Kahan or FP64 sums (FP64: plain FP64
-// partials folded with compensation); j sums: a sweep's terms (128 a wave, four waves).  Every slot
-// row is written once; k_fine_reduce adds a row's j slots, carries and i sums in a fixed order in
-// FP64 with compensation, so results repeat bit for bit.
+// Sums.  i sums: FP32 partials of a sweep (64 terms) folded into Kahan or FP64 sums (FP64: plain FP64
+// partials folded with compensation).  j sums: a wave's terms of a sweep in the law's type, 128 with
+// two i chunks and 256 with four, and the four waves' sums in FP64.  FP32 chains of at most 256 are what
+// the one-sided kernels add before they fold, and like theirs the slots are FP64 (`wide`) below the
+// coarser tiles' sizes; from there on FP32 as those tiles' are.  Every slot row is written once;
+// k_fine_reduce adds a row's j slots, carries and i sums in a fixed order in FP64 with compensation, so
+// results repeat bit for bit.
 #include "allpairs.h"
 #include "fine.h"
 
@@ -320,6 +323,16 @@ template <class Op, int I> constexpr int fine_waves_per_eu()
     return Op::NC >= 6 ? 3 : 4;
 }
 
+// the i sums of a wave's chunks, one slot row a lane and chunk
+template <typename S, int NC, int NCP, int PREC, int I>
+__device__ __forceinline__ void put_sums(S *dst, const RunSum<PREC> (&acc)[I][NC])
+{
+#pragma unroll
+    for (int k = 0; k < I; ++k)
+#pragma unroll
+        for (int c = 0; c < NCP; ++c) dst[k * kWave * NCP + c] = c < NC ? (S)acc[k][c < NC ? c : 0].value() : S(0);
+}
+
 }  // namespace
 
 template <class Op, int PREC, int I>
@@ -427,22 +440,20 @@ void k_fine(FineLaunch a)
         // have all reached this barrier's predecessor.
         __syncthreads();
         {
-            T *dst = s0 == 0 ? (T *)a.jslot + (int64_t)(fine_jslot(b, nb, kRows) + jc * kWave) * NCP
-                             : (T *)a.carry + (int64_t)wg * kWave * NCP;
+            void *dst = s0 == 0 ? a.jslot : a.carry;
+            const int64_t at = s0 == 0 ? (int64_t)(fine_jslot(b, nb, kRows) + jc * kWave) * NCP : (int64_t)wg * kWave * NCP;
             for (int e = threadIdx.x; e < kWave * NCP; e += kFineWaves * kWave) {
-                T v = (&jr[buf][0][0][0])[e];
+                double v = (double)(&jr[buf][0][0][0])[e];
 #pragma unroll
-                for (int x = 1; x < kFineWaves; ++x) v += (&jr[buf][x][0][0])[e];
-                dst[e] = v;
+                for (int x = 1; x < kFineWaves; ++x) v += (double)(&jr[buf][x][0][0])[e];
+                if (sizeof(T) == 8 || a.wide) ((double *)dst)[at + e] = v;
+                else ((float *)dst)[at + e] = (float)v;
             }
         }
         if (!more || over) {
-            T *dst = (T *)a.islot + (int64_t)(wg + b) * kRows * NCP;
-#pragma unroll
-            for (int k = 0; k < I; ++k)
-#pragma unroll
-                for (int c = 0; c < NCP; ++c)
-                    dst[((w * I + k) * kWave + lane) * NCP + c] = c < NC ? (T)acc[k][c < NC ? c : 0].value() : T(0);
+            const int64_t at = ((int64_t)(wg + b) * kRows + w * I * kWave + lane) * NCP;
+            if (sizeof(T) == 8 || a.wide) put_sums<double, NC, NCP>((double *)a.islot + at, acc);
+            else put_sums<float, NC, NCP>((float *)a.islot + at, acc);
             if (!more) return;
             ++b;
             load_block();
@@ -459,7 +470,7 @@ void k_fine(FineLaunch a)
 // few rows and up to a hundred terms a row), each wave adding its own in order, and the waves' sums
 // merged in wave order, all in FP64 with compensation.  The operator's epilogue is separate for each
 // column.
-template <typename T, int NCP>
+template <typename T, typename S, int NCP>
 __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
 {
     __shared__ double part[kRedWaves][2][kWave];
@@ -471,9 +482,9 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
     const int jc = (int)(blockIdx.x / NCP);                     // 64 (row, column) pairs lie in one chunk
     const int ch = kFineWaves * a.ich, rows = ch * kWave;        // of a block
     const int b = jc / ch, nch = a.nch, per = a.per;
-    const T *__restrict__ jslot = (const T *)a.jslot + t;
-    const T *__restrict__ carry = (const T *)a.carry + (t - (int64_t)jc * kWave * NCP);
-    const T *__restrict__ islot = (const T *)a.islot + (t - (int64_t)b * rows * NCP);
+    const S *__restrict__ jslot = (const S *)a.jslot + t;
+    const S *__restrict__ carry = (const S *)a.carry + (t - (int64_t)jc * kWave * NCP);
+    const S *__restrict__ islot = (const S *)a.islot + (t - (int64_t)b * rows * NCP);
     NSum v;
     // fine_jslot(k), kRedWaves blocks a time
     int at = fine_jslot(w, a.nb, rows), step = rows * kRedWaves * (2 * (a.nb - w) - kRedWaves - 1) / 2;
@@ -598,9 +609,11 @@ hipError_t launch_fine_reduce(const FineLaunch &a, hipStream_t s)
     if (!fine_valid(a)) return hipErrorInvalidValue;
     const int cols = fine_cols(a.op);
     const dim3 grid((unsigned)(a.nch * cols)), block(kRedWaves * kWave);
-    if (a.prec == P_FP64) hipLaunchKernelGGL((k_fine_reduce<double, 4>), grid, block, 0, s, a);
-    else if (cols == 4) hipLaunchKernelGGL((k_fine_reduce<float, 4>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_fine_reduce<float, 8>), grid, block, 0, s, a);
+    if (a.prec == P_FP64) hipLaunchKernelGGL((k_fine_reduce<double, double, 4>), grid, block, 0, s, a);
+    else if (cols == 4 && a.wide) hipLaunchKernelGGL((k_fine_reduce<float, double, 4>), grid, block, 0, s, a);
+    else if (cols == 4) hipLaunchKernelGGL((k_fine_reduce<float, float, 4>), grid, block, 0, s, a);
+    else if (a.wide) hipLaunchKernelGGL((k_fine_reduce<float, double, 8>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_fine_reduce<float, float, 8>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
