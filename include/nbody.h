@@ -33,13 +33,13 @@
  * kernels do (Section 2, the remark on Newton's third law).  For gravity and
  * the LJC laws over a whole system, FP32 pair arithmetic, the symmetric pair
  * tiles (j_stage 2,
- * the default for the forces from N = 32,768 to 2,097,152) evaluate each unordered pair once
+ * the default for the forces above N = 65,536, to 2,097,152) evaluate each unordered pair once
  * and apply it to both particles through per-block partial sums that a
  * fixed-order reduction adds, without atomics; the batched entry point has
  * symmetric tiles of its own for gravity and LJC ensembles.  Fine pair tiles
- * (j_stage 3) do the same in smaller work units from about 2,048 particles,
- * FP64 pair arithmetic included, and row groups finish the forces of smaller
- * systems in one launch.  Either way results are deterministic run to run.
+ * (j_stage 3) do the same in smaller work units between them and the row
+ * groups, one-sided kernels that finish the forces of up to 4,096 particles in
+ * one launch, and for FP64 forces up to 262,144.  Either way results are deterministic run to run.
  *
  * Conventions shared by every entry point
  * ---------------------------------------
@@ -224,10 +224,12 @@ typedef struct nbody_exclusions {
  *             The rule's choice above the row groups: for FP32 up to 32,767
  *             particles (forces and leapfrog of every law, gravity's backward,
  *             LJC(linear)'s from 2,560 to 16,383 atoms, the shared Hermite
- *             steps), for FP64 everywhere it applies.  Where the rule reports
- *             j_stage 2, up to 65,536 particles, a launch whose configuration is
- *             neither forced nor tuned runs them too (not the jerk and
- *             LJC(linear)'s backward). */
+ *             steps), for FP64 everywhere it applies.  From 32,768 to 65,536
+ *             particles in FP32 (not the jerk and LJC(linear)'s backward) the
+ *             rule reports a shape of j_stage 2, and that shape runs as the fine
+ *             tiles, also when it is forced or tuned as reported; any other
+ *             shape of j_stage 2 runs the symmetric tiles it names.  The
+ *             autotuners time the fine tiles there. */
 typedef struct nbody_config {
     int32_t block;
     int32_t i_per_lane;
@@ -259,8 +261,9 @@ int nbody_forces(const double *pos, const double *params, int64_t n, const nbody
  * live in a device scratch area of 64 MiB that the library holds on each GPU
  * it runs on until the process ends (looked up once per device on the first
  * call there).  The arguments mean what they mean for nbody_forces; the
- * result is the same evaluation, up to the rounding of a j split that may be
- * smaller (so that its partials fit the scratch area).
+ * result is the same evaluation, up to the rounding of sums that are cut
+ * otherwise where the chosen kernel's partials do not fit the scratch area (a
+ * smaller j split, or the symmetric or one-sided kernels for the fine tiles).
  * Limit: n <= 67,108,864 / record bytes - 64, i.e. 4,194,240 particles for
  * FP32 gravity, 2,097,088 for FP32 LJC and FP64 gravity, 1,048,512 for FP64
  * LJC; larger n is refused with NBODY_EINVAL before anything is enqueued.
@@ -295,9 +298,11 @@ int nbody_forces_subset(const double *pos, const double *params, int64_t n, cons
  * (optional) receive, for EVERY row, the FP64 sum of that row's contributions
  * from the share's tiles, scaled as nbody_forces scales them (G, -G for
  * gravity; 1 and 1/2 or 1 for LJC); rows
- * the share does not touch get zero.  The sum over all shares equals
- * nbody_forces' result up to the rounding of the final FP64 additions; with
- * n_shares = 1 it is that result.
+ * the share does not touch get zero.  Where nbody_forces runs the symmetric
+ * tiles (j_stage 2; by the rule above 65,536 particles), the sum over all
+ * shares equals its result up to the rounding of the final FP64 additions, and
+ * with n_shares = 1 it is that result; elsewhere the two differ by the
+ * rounding of FP32 sums.
  *  share, n_shares   0 <= share < n_shares.
  * Law: any, with NBODY_FP32_KAHAN or NBODY_FP32_FP64ACC, n <= 2,097,152
  * (NBODY_ENOTSUP otherwise: FP64 and FP32_PLAIN shard by rows, with
@@ -481,9 +486,10 @@ int nbody_forces_jerk(const double *pos, const double *vel, const double *mass, 
  *  device.  law as nbody_forces_jerk.  dt > 0 finite, nsteps >= 0.  The
  *  update is FP64; the pair arithmetic follows law->precision.  Each step
  *  evaluates every particle as nbody_forces_jerk would for the whole system
- *  where its configuration (NBODY_API_JERK) selects the symmetric tiles, over
- *  the fine tiles from 2,048 to 32,767 particles where neither configuration
- *  is forced or tuned, and otherwise with the NBODY_API_HERMITE configuration.
+ *  where its configuration (NBODY_API_JERK) selects the symmetric or the fine
+ *  tiles; over the fine tiles (FP32) from 2,048 to 32,767 particles where both
+ *  configurations are the rule's, forced or tuned as reported or not; and
+ *  otherwise with the NBODY_API_HERMITE configuration.
  * Workspace: nbody_workspace_bytes(NBODY_API_HERMITE, n, 1, law). */
 int hermite_step(double *pos, double *vel, double *acc, double *jerk, const double *mass,
                  int64_t n, const nbody_law *law, double dt, int32_t nsteps, void *ws,

@@ -320,6 +320,12 @@ struct Cfg {
     int block = 256, ipl = 1, j_tile = 256, j_split = 1, j_stage = 0;
 };
 
+bool same_cfg(const Cfg &a, const Cfg &b)
+{
+    return a.block == b.block && a.ipl == b.ipl && a.j_tile == b.j_tile && a.j_split == b.j_split &&
+           a.j_stage == b.j_stage;
+}
+
 std::mutex g_mu;
 constexpr int kNumApi = 7;
 bool g_override_set[kNumApi] = {false, false, false, false, false, false, false};
@@ -696,40 +702,59 @@ void tune_cache_store()
         fprintf(stderr, "nbody: tuning cache %s not written: %s\n", p, nbody_last_error());
 }
 
+// Whether c is the shape that the rule reports for a whole system of n (with the potential or without:
+// nbody_get_config names one of them)
+bool is_rule_shape(const Cfg &c, int api, int law, int prec, int64_t n)
+{
+    const int64_t npad = round_up(std::max<int64_t>(n, 1), 64);
+    for (bool pot : {false, true})
+        if (same_cfg(c, sanitize(heuristic(api, law, prec, n, n, 1, pot), api, law, prec, npad))) return true;
+    return false;
+}
+
 // The configuration for n output rows in S systems; nj j records (0: nj = n).
-// ruled (or null): whether it is the rule's, neither forced nor tuned.
+// ruled (or null; whole systems): whether it is the rule's, also where it was forced or tuned as reported
+// and that makes a difference.
 Cfg choose(int api, const nbody_law *law, int64_t n, int64_t S, bool pot, int64_t nj = 0, bool *ruled = nullptr)
 {
     tune_cache_load_once();
-    if (ruled) *ruled = false;
     if (nj <= 0) nj = n;
     const int64_t npad = round_up(std::max<int64_t>(std::max(n, nj), 1), 64);
-    std::lock_guard<std::mutex> lk(g_mu);
-    if (g_override_set[api]) return sanitize(g_override[api], api, law->kind, law->precision, npad);
-    const int sb = tune_sbucket(api, S, nj);
-    auto it = g_tuned.find(TuneKey(api, law->kind, law->precision, pot ? 1 : 0, size_bucket(n), sb));
-    if (it == g_tuned.end() && (api == NBODY_API_LEAPFROG || api == NBODY_API_HERMITE))
-        // a leapfrog step runs the forces kernel, a Hermite step the jerk kernel
-        it = g_tuned.find(TuneKey(api == NBODY_API_LEAPFROG ? NBODY_API_FORCES : NBODY_API_JERK,
-                                  law->kind, law->precision, pot ? 1 : 0, size_bucket(n), sb));
-    // (the jerk's symmetric tiles evaluate whole systems: not a shape for the block steps, which
-    // a shared Hermite step takes from the jerk's own configuration)
-    if (it != g_tuned.end() && api == NBODY_API_HERMITE && it->second.first.j_stage >= kSymStage)
-        it = g_tuned.end();
-    if (it != g_tuned.end()) return sanitize(it->second.first, api, law->kind, law->precision, npad);
-    if (ruled) *ruled = true;
-    return heuristic(api, law->kind, law->precision, n, nj, S, pot);
+    Cfg c;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        const int sb = tune_sbucket(api, S, nj);
+        auto it = g_tuned.find(TuneKey(api, law->kind, law->precision, pot ? 1 : 0, size_bucket(n), sb));
+        if (it == g_tuned.end() && (api == NBODY_API_LEAPFROG || api == NBODY_API_HERMITE))
+            // a leapfrog step runs the forces kernel, a Hermite step the jerk kernel
+            it = g_tuned.find(TuneKey(api == NBODY_API_LEAPFROG ? NBODY_API_FORCES : NBODY_API_JERK,
+                                      law->kind, law->precision, pot ? 1 : 0, size_bucket(n), sb));
+        // (the jerk's symmetric tiles evaluate whole systems: not a shape for the block steps, which
+        // a shared Hermite step takes from the jerk's own configuration)
+        if (it != g_tuned.end() && api == NBODY_API_HERMITE && it->second.first.j_stage >= kSymStage)
+            it = g_tuned.end();
+        if (!g_override_set[api] && it == g_tuned.end()) {
+            if (ruled) *ruled = true;
+            return heuristic(api, law->kind, law->precision, n, nj, S, pot);
+        }
+        c = sanitize(g_override_set[api] ? g_override[api] : it->second.first, api, law->kind, law->precision, npad);
+    }
+    // (asked only where the rule's shape runs as another: run_cfg, and the shared Hermite steps)
+    if (ruled)
+        *ruled = n == nj && (c.j_stage == kSymStage ? n <= kFineForSym : api == NBODY_API_JERK) &&
+                 is_rule_shape(c, api, law->kind, law->precision, n);
+    return c;
 }
 
 // The configuration that runs for c, the rule's (ruled) or not, over a whole system of n: the fine
 // tiles in the place of the rule's coarser ones up to kFineForSym particles.
-Cfg run_cfg(const Cfg &c, bool ruled, int api, const nbody_law *law, int64_t n)
+Cfg run_cfg(const Cfg &c, bool ruled, int api, int law, int prec, int64_t n)
 {
-    if (!ruled || c.j_stage != kSymStage || n > kFineForSym || !sym_eligible(api, law->kind, law->precision)) return c;
+    if (!ruled || c.j_stage != kSymStage || n > kFineForSym || !sym_eligible(api, law, prec)) return c;
     Cfg f = c;
     f.j_stage = kFineStage;
     f.ipl = kFineIch4;                                // (two where four are not built)
-    return sanitize(f, api, law->kind, law->precision, round_up(n, 64));
+    return sanitize(f, api, law, prec, round_up(n, 64));
 }
 
 // c, or the rule's one-sided configuration when c selects the symmetric tiles
@@ -2002,7 +2027,7 @@ int forces_impl(const double *pos, const double *params, int64_t n, const int64_
     Cfg c = sanitize(forced ? *forced : choose(NBODY_API_FORCES, law, nrows, 1, pot, n, &ruled), NBODY_API_FORCES,
                      law->kind, law->precision, round_up(std::max(n, nrows), 64));
     if (rows || excl) c = one_sided(c, NBODY_API_FORCES, law, nrows, n, pot);
-    else c = run_cfg(c, ruled, NBODY_API_FORCES, law, n);
+    else c = run_cfg(c, ruled, NBODY_API_FORCES, law->kind, law->precision, n);
     const Cfg cs = with_excl(sanitize(c, NBODY_API_FORCES, law->kind, law->precision,
                                       round_up(std::max(n, nrows), 64)), excl != nullptr);
     return run_forward(law, cs, pos, params, n, rows, nrows, make_epi(law, out_force, out_potential),
@@ -2074,21 +2099,18 @@ int batched_impl(const int64_t *offsets, int64_t S, const double *pos, const dou
 // candidate list for the measured search
 std::vector<Cfg> candidate_set(int api, int law, int prec, int64_t n, bool pot);
 
-bool same_cfg(const Cfg &a, const Cfg &b)
-{
-    return a.block == b.block && a.ipl == b.ipl && a.j_tile == b.j_tile && a.j_split == b.j_split &&
-           a.j_stage == b.j_stage;
-}
-
-// The configurations the autotuners time, the heuristic's own choice first:
+// The configurations the autotuners time, the one that the rule runs first:
 // with kTuneMargin, a measured near-tie keeps it, so the choice repeats across
-// runs and devices of one kind.
+// runs and devices of one kind.  A shape that the rule reports and runs as another
+// (run_cfg) is no candidate: chosen, it would run as that other again.
 std::vector<Cfg> candidates(int api, int law, int prec, int64_t n, bool pot)
 {
-    std::vector<Cfg> out{sanitize(heuristic(api, law, prec, n, n, 1, pot), api, law, prec,
-                                  round_up(std::max<int64_t>(n, 1), 64))};
+    const Cfg rule = sanitize(heuristic(api, law, prec, n, n, 1, pot), api, law, prec,
+                              round_up(std::max<int64_t>(n, 1), 64));
+    std::vector<Cfg> out{run_cfg(rule, true, api, law, prec, n)};
+    const bool replaced = !same_cfg(out[0], rule);
     for (const Cfg &c : candidate_set(api, law, prec, n, pot))
-        if (!same_cfg(c, out[0])) out.push_back(c);
+        if (!same_cfg(c, out[0]) && !(replaced && is_rule_shape(c, api, law, prec, n))) out.push_back(c);
     return out;
 }
 
@@ -2270,9 +2292,11 @@ std::vector<Cfg> candidate_set(int api, int law, int prec, int64_t n, bool pot)
 // all n rows is therefore at most max_split(npad).  A forced configuration's
 // split instead, held to the same bounds.  Built once per law, size, kernel
 // shape and configuration state.
-std::shared_ptr<const std::vector<int>> hermite_split_table(const nbody_law *law, int64_t n, const Cfg &c)
+// (by_rule: whatever is forced)
+std::shared_ptr<const std::vector<int>> hermite_split_table(const nbody_law *law, int64_t n, const Cfg &c,
+                                                            bool by_rule = false)
 {
-    using Key = std::tuple<int, int64_t, int, int, int, uint64_t>;
+    using Key = std::tuple<int, int64_t, int, int, int, uint64_t, bool>;
     static std::mutex mu;
     static std::vector<std::pair<Key, std::shared_ptr<const std::vector<int>>>> cache;   // most recent last
     uint64_t ver;
@@ -2280,9 +2304,9 @@ std::shared_ptr<const std::vector<int>> hermite_split_table(const nbody_law *law
     {
         std::lock_guard<std::mutex> lk(g_mu);
         ver = g_cfg_version;
-        if (g_override_set[NBODY_API_HERMITE]) forced = g_override[NBODY_API_HERMITE].j_split;
+        if (g_override_set[NBODY_API_HERMITE] && !by_rule) forced = g_override[NBODY_API_HERMITE].j_split;
     }
-    const Key key(law->precision, n, c.ipl, c.block, c.j_stage, ver);
+    const Key key(law->precision, n, c.ipl, c.block, c.j_stage, ver, by_rule);
     {
         std::lock_guard<std::mutex> lk(mu);
         for (size_t k = 0; k < cache.size(); ++k)
@@ -2461,8 +2485,22 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
     hipError_t e = scratch_area(&base);
     if (e != hipSuccess) return hip_fail(e, "scratch area");
     const bool pot = out_potential != nullptr;
-    Cfg c = sanitize(choose(NBODY_API_FORCES, law, n, 1, pot, n), NBODY_API_FORCES, law->kind,
+    bool ruled;
+    Cfg c = sanitize(choose(NBODY_API_FORCES, law, n, 1, pot, n, &ruled), NBODY_API_FORCES, law->kind,
                      law->precision, npad);
+    // the fine tiles (or row groups) when their padded records and slots fit the area
+    const Cfg f = run_cfg(c, ruled, NBODY_API_FORCES, law->kind, law->precision, n);
+    if (f.j_stage == kFineStage) {
+        FwdWs lay{};
+        lay.part_off = align256((size_t)fine_npad(n, f.ipl) * rbytes);
+        lay.scratch_off = lay.total = kScratchBytes;
+        if (is_rows(f) || lay.part_off + fine_launch_bytes(n, f.ipl, FINE_FORCE, law->precision) <= kScratchBytes)
+            return run_forward(law, f, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot,
+                               base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
+        if (c.j_stage == kFineStage)
+            c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
+                         law->precision, npad);
+    }
     if (c.j_stage == kSymStage) {
         // the symmetric tiles when their padded records and slot partials fit the area
         // (the chosen block edge, else the larger one, which needs fewer partials)
@@ -2484,17 +2522,6 @@ int nbody_forces_noalloc(const double *pos, const double *params, int64_t n, con
             return run_forward(law, cb, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential),
                                pot, base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
         }
-        c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
-                     law->precision, npad);
-    }
-    if (c.j_stage == kFineStage) {
-        // likewise the fine tiles' records and slots
-        FwdWs lay{};
-        lay.part_off = align256((size_t)fine_npad(n, c.ipl) * rbytes);
-        lay.scratch_off = lay.total = kScratchBytes;
-        if (is_rows(c) || lay.part_off + fine_launch_bytes(n, c.ipl, FINE_FORCE, law->precision) <= kScratchBytes)
-            return run_forward(law, c, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot,
-                               base, lay, (hipStream_t)stream, nullptr, ExclArgs{}, false);
         c = sanitize(one_sided(c, NBODY_API_FORCES, law, n, n, pot), NBODY_API_FORCES, law->kind,
                      law->precision, npad);
     }
@@ -2561,7 +2588,7 @@ int backward_impl(const double *pos, const double *params, int64_t n, const nbod
     bool ruled;
     Cfg c = sanitize(choose(NBODY_API_BACKWARD, law, n, 1, false, 0, &ruled), NBODY_API_BACKWARD, law->kind,
                      law->precision, round_up(n, 64));
-    if (!excl) c = run_cfg(c, ruled, NBODY_API_BACKWARD, law, n);
+    if (!excl) c = run_cfg(c, ruled, NBODY_API_BACKWARD, law->kind, law->precision, n);
     if (excl && c.j_stage == kFineStage)              // the fine tiles take no exclusion lists
         c = sanitize(one_sided(c, NBODY_API_BACKWARD, law, n, n, false), NBODY_API_BACKWARD, law->kind,
                      law->precision, round_up(n, 64));
@@ -2978,7 +3005,9 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
     hipStream_t s = (hipStream_t)stream;
     char *base = (char *)ws;
     if (nsteps == 0) {
-        const Cfg c = choose(NBODY_API_LEAPFROG, law, n, 1, true);
+        bool ruled;
+        Cfg c = choose(NBODY_API_LEAPFROG, law, n, 1, true, 0, &ruled);
+        c = run_cfg(c, ruled, NBODY_API_LEAPFROG, law->kind, law->precision, n);
         return run_forward(law, c, pos, params, n, nullptr, n,
                            make_epi(law, (double *)(base + lay.scratch_off), out_potential), true, ws,
                            lay, s, nullptr);
@@ -2988,8 +3017,8 @@ int leapfrog_step(double *pos, double *vel, double *acc, const double *params,
     bool rule_mid, rule_end;
     Cfg mid = choose(NBODY_API_LEAPFROG, law, n, 1, false, 0, &rule_mid);
     Cfg end = out_potential ? choose(NBODY_API_LEAPFROG, law, n, 1, true, 0, &rule_end) : mid;
-    end = run_cfg(end, out_potential ? rule_end : rule_mid, NBODY_API_LEAPFROG, law, n);
-    mid = run_cfg(mid, rule_mid, NBODY_API_LEAPFROG, law, n);
+    end = run_cfg(end, out_potential ? rule_end : rule_mid, NBODY_API_LEAPFROG, law->kind, law->precision, n);
+    mid = run_cfg(mid, rule_mid, NBODY_API_LEAPFROG, law->kind, law->precision, n);
     bool packed = false, other = false;
     for (int32_t k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
@@ -3055,6 +3084,12 @@ int hermite_step(double *pos, double *vel, double *acc, double *jerk, const doub
     Cfg c = sanitize(choose(NBODY_API_HERMITE, law, n, 1, false, n, &ruled_h), NBODY_API_HERMITE, law->kind,
                      law->precision, round_up(n, 64));
     c.j_split = hermite_split_table(law, n, c)->back();   // the block steps' rule for all n rows
+    if (!ruled_h) {      // as reported, with the split for all rows
+        Cfg r = sanitize(heuristic(NBODY_API_HERMITE, law->kind, law->precision, n, n, 1, false), NBODY_API_HERMITE,
+                         law->kind, law->precision, round_up(n, 64));
+        r.j_split = hermite_split_table(law, n, r, true)->back();
+        ruled_h = same_cfg(c, r);
+    }
     // a shared step evaluates every row: the symmetric tiles where the acceleration-and-jerk
     // entry point's configuration for the whole system selects them, and by rule the fine tiles
     // below their sizes (1.4x the one-sided step at 30,011 particles).  The acceleration-and-jerk
