@@ -300,9 +300,10 @@ int nbody_forces_subset(const double *pos, const double *params, int64_t n, cons
  * gravity; 1 and 1/2 or 1 for LJC); rows
  * the share does not touch get zero.  Where nbody_forces runs the symmetric
  * tiles (j_stage 2; by the rule above 65,536 particles), the sum over all
- * shares equals its result up to the rounding of the final FP64 additions, and
- * with n_shares = 1 it is that result; elsewhere the two differ by the
- * rounding of FP32 sums.
+ * shares equals its result up to the rounding of the final FP64 additions;
+ * elsewhere the two differ by the rounding of FP32 sums.  With n_shares = 1 it
+ * is nbody_forces' result wherever j_stage 2 is reported (by the rule from
+ * 32,768 particles).
  *  share, n_shares   0 <= share < n_shares.
  * Law: any, with NBODY_FP32_KAHAN or NBODY_FP32_FP64ACC, n <= 2,097,152
  * (NBODY_ENOTSUP otherwise: FP64 and FP32_PLAIN shard by rows, with

@@ -2058,7 +2058,15 @@ int share_impl(const double *pos, const double *params, int64_t n, const nbody_l
     if (rc) return rc;
     const bool pot = out_potential != nullptr;
     const int64_t npad = round_up(n, 64);
-    Cfg c = choose(NBODY_API_FORCES, law, n, 1, pot);
+    bool ruled;
+    Cfg c = choose(NBODY_API_FORCES, law, n, 1, pot, 0, &ruled);
+    // the only share is nbody_forces' result where that reports the tiles
+    if (n_shares == 1) {
+        const Cfg f = run_cfg(c, ruled, NBODY_API_FORCES, law->kind, law->precision, n);
+        if (c.j_stage == kSymStage && f.j_stage != kSymStage)
+            return run_forward(law, f, pos, params, n, nullptr, n, make_epi(law, out_force, out_potential), pot, ws, lay,
+                               (hipStream_t)stream, nullptr);
+    }
     if (c.j_stage != kSymStage) {                      // the rule's symmetric shape for this size
         c = Cfg{};
         c.j_stage = kSymStage;

@@ -99,6 +99,13 @@ def test_allocation_free_call_runs_the_same_kernel(nb, law):
     assert same(nb.forces(X, P, lw, potential=False), nb.forces_noalloc(X, P, lw, potential=False))
 
 
+@pytest.mark.parametrize("law", ["gravity", "ljc"])
+def test_the_only_share_is_the_forces_result(nb, law):
+    X, P, _, lw = system(nb, law)
+    assert same(nb.forces(X, P, lw), nb.forces_share(X, P, lw, 0, 1))
+    assert same(nb.forces(X, P, lw, potential=False), nb.forces_share(X, P, lw, 0, 1, potential=False))
+
+
 CHILD = r"""
 import sys
 sys.path.insert(0, %(root)r)
