@@ -112,7 +112,11 @@ enum nbody_precision {
  * tiles from 32,768 particles on, a tile's sum for a particle is stored in
  * FP32 between two kernels, under either running sum, and the j side of a
  * symmetric tile is a plain FP32 sum over the tile's rows (256, 1024 or 2048);
- * these are then added in FP64. */
+ * these are then added in FP64.
+ * Range in FP32: for gravity's forces and jerk the one-sided kernels, the row
+ * groups and the fine tiles below 32,768 particles form m / s^3 as (m / s) /
+ * s^2; the other tiles form m s^-3, and the adjoints s^-3 everywhere, for
+ * which distances must lie between about 2e-13 and 4e12 units. */
 
 /* Law parameters (host struct).  `softening` is the length eps of Eq. 1 (the
  * kernel adds eps^2 to r^2, as the Appendix listing adds its constant).

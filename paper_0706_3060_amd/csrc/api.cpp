@@ -166,8 +166,9 @@ constexpr int64_t kFineAdjLjcMinN = 4097;
 // without them 52 against 53 at 12,000, 77 against 78 at 16,000, 112 against 107 at 20,000, 225 against
 // 207 at 30,011).
 constexpr int64_t kFineMin4 = 20480;
-// Above this size only four chunks, where they are built: two take twice the slots and are slower.
-constexpr int64_t kFineMax2 = int64_t(1) << 15;
+// From this size (padded to 64) only four chunks, where they are built: two take twice the slots and are
+// slower, and FP32 gravity has them with FP64 slots only (fine_wide).
+constexpr int64_t kFineEnd2 = kSymMinN;
 // Where the rule says the coarser tiles (j_stage 2), the fine tiles still run up to this size: against
 // them per call (us) at 33,000 particles LJC(linear) with energies 385 against 451, gravity's adjoint
 // 380 against 447; at 65,536 gravity 871 against 889 (963 against 964 with potentials), LJC(linear)
@@ -211,8 +212,8 @@ int64_t fine_npad(int64_t n, int ich) { return (int64_t)fine_blocks(n, ich) * kF
 int fine_quarters(int64_t n, int ich) { return fine_begin(fine_blocks(n, ich), fine_chunks(n), kFineWaves * ich); }
 // most workgroups a launch over n particles has: four quarters of a sweep each at least
 int fine_wgs_bound(int64_t n, int ich) { return std::min(kFineMaxWgs, (fine_quarters(n, ich) + 3) / 4); }
-// FP32 pair arithmetic: FP64 slots where the one-sided kernels would run, whose j parts are FP64, and
-// FP32 slots from the coarser tiles' sizes on, as theirs are
+// FP32 pair arithmetic: FP64 slots where the one-sided kernels would run, whose j parts are FP64 (and for
+// gravity their order of factors), and FP32 slots from the coarser tiles' sizes on, as theirs are
 bool fine_wide(int64_t n, int prec) { return !is_f32(prec) || n < kSymMinN; }
 // slot buffers: the blocks' j sums, the workgroups' i sums and their carries, one after another
 struct FineSlots {
@@ -232,7 +233,7 @@ size_t fine_partial_bytes(int64_t n, int ich, int op, int prec)
     return fine_slots(n, ich, fine_wgs_bound(n, ich), op, prec).total;
 }
 // what a workspace holds for the fine tiles: records and slots of the shapes that may run at this size
-bool fine_two(int64_t npad, int op, int law, int prec) { return npad <= kFineMax2 || !fine_has4(op, law, prec); }
+bool fine_two(int64_t npad, int op, int law, int prec) { return npad < kFineEnd2 || !fine_has4(op, law, prec); }
 int64_t fine_records(int64_t n) { return std::max(fine_npad(n, kFineIch), fine_npad(n, kFineIch4)); }
 size_t fine_part(int64_t n, int op, int law, int prec)
 {

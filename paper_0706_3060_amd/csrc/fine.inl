@@ -57,7 +57,10 @@ __device__ __forceinline__ double next_dpp(double v)
 // Each: record type Rec (kCols values of T, of which the pair reads the first kStage), the sums NC per
 // particle, how many of them move through the crossbar, and the pair.  own marks the particle's own
 // pair, which contributes nothing; JS: add the j side.
-template <typename PT, bool POT> struct GravOp {
+// FAR: m / s^3 as (m / s) / s^2, the one-sided kernels' order, whose range holds FP32 masses and
+// distances in SI units; otherwise m times s^-3, the coarser tiles', a multiplication less for the two
+// particles and out of FP32's range for distances above 4e12 or below 2e-13.
+template <typename PT, bool POT, bool FAR = false> struct GravOp {
     using T = PT;
     struct alignas(16) Rec { T x, y, z, m; };
     static constexpr int kCols = 4, kStage = 4, NC = POT ? 4 : 3, kCross = sizeof(T) == 8 ? 0 : 3;
@@ -73,14 +76,15 @@ template <typename PT, bool POT> struct GravOp {
         r2 = own ? T(1) : r2;
         mj = own ? T(0) : mj;
         const T ri = rsqrt_(r2);
-        const T ri3 = (ri * ri) * ri;
-        const T cj = mj * ri3;
+        const T ri2 = ri * ri;
+        const T ri3 = ri2 * ri;
+        const T cj = FAR ? (mj * ri) * ri2 : mj * ri3;
         p[0] = fma_(cj, dx, p[0]);
         p[1] = fma_(cj, dy, p[1]);
         p[2] = fma_(cj, dz, p[2]);
         if constexpr (POT) p[3] = fma_(mj, ri, p[3]);
         if constexpr (JS) {
-            const T ci = I.m * ri3;
+            const T ci = FAR ? (I.m * ri) * ri2 : I.m * ri3;
             jv[0] = fma_(-ci, dx, jv[0]);
             jv[1] = fma_(-ci, dy, jv[1]);
             jv[2] = fma_(-ci, dz, jv[2]);
@@ -213,7 +217,7 @@ struct LjcAdjOp {
 };
 
 // Acceleration and jerk: with w = v_j - v_i and u = w - 3 (d.w) d / s^2, i gets m_j d / s^3 and
-// m_j u / s^3, j the same with -m_i.
+// m_j u / s^3, j the same with -m_i (m / s^3 as (m / s) / s^2, as in GravOp).
 template <bool POT> struct JerkOp {
     using T = float;
     struct alignas(16) Rec { T x, y, z, m, vx, vy, vz, p0; };
@@ -232,13 +236,12 @@ template <bool POT> struct JerkOp {
         mj = own ? 0.0f : mj;
         const T ri = rsqrt_(r2);
         const T ri2 = ri * ri;
-        const T ri3 = ri2 * ri;
         T dw = dx * wx;
         dw = fma_(dy, wy, dw);
         dw = fma_(dz, wz, dw);
         const T q = (dw * ri2) * -3.0f;
         const T ux = fma_(q, dx, wx), uy = fma_(q, dy, wy), uz = fma_(q, dz, wz);
-        const T cj = mj * ri3;
+        const T cj = (mj * ri) * ri2;
         p[0] = fma_(cj, dx, p[0]);
         p[1] = fma_(cj, dy, p[1]);
         p[2] = fma_(cj, dz, p[2]);
@@ -247,7 +250,7 @@ template <bool POT> struct JerkOp {
         p[5] = fma_(cj, uz, p[5]);
         if constexpr (POT) p[6] = fma_(mj, ri, p[6]);
         if constexpr (JS) {
-            const T ci = I.m * ri3;
+            const T ci = (I.m * ri) * ri2;
             jv[0] = fma_(-ci, dx, jv[0]);
             jv[1] = fma_(-ci, dy, jv[1]);
             jv[2] = fma_(-ci, dz, jv[2]);
@@ -529,12 +532,17 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
     }
 }
 
+static dim3 fine_grid(const FineLaunch &a) { return dim3((unsigned)((a.nwg + kSymXcds - 1) / kSymXcds * kSymXcds)); }
+template <class Op, int PREC> static void fine_go4(const FineLaunch &a, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_fine<Op, PREC, kFineIch4>), fine_grid(a), dim3(kFineWaves * kWave), 0, s, a);
+}
 template <class Op, int PREC, bool FOUR> static void fine_go(const FineLaunch &a, hipStream_t s)
 {
-    const dim3 grid((unsigned)((a.nwg + kSymXcds - 1) / kSymXcds * kSymXcds)), block(kFineWaves * kWave);
+    const dim3 grid = fine_grid(a), block(kFineWaves * kWave);
     if constexpr (FOUR)
         if (a.ich == kFineIch4) {
-            hipLaunchKernelGGL((k_fine<Op, PREC, kFineIch4>), grid, block, 0, s, a);
+            fine_go4<Op, PREC>(a, s);
             return;
         }
     hipLaunchKernelGGL((k_fine<Op, PREC, kFineIch>), grid, block, 0, s, a);
@@ -544,10 +552,19 @@ template <class Op, bool FOUR> static void fine_go32(const FineLaunch &a, hipStr
     if (a.prec == P_KAHAN) fine_go<Op, P_KAHAN, FOUR>(a, s);
     else fine_go<Op, P_FP64ACC, FOUR>(a, s);
 }
-template <template <typename, bool> class Op, bool POT, bool FOUR32> static void fine_go_law(const FineLaunch &a, hipStream_t s)
+template <template <typename, bool> class Op, bool POT> static void fine_go_law(const FineLaunch &a, hipStream_t s)
 {
     if (a.prec == P_FP64) fine_go<Op<double, POT>, P_FP64, true>(a, s);
-    else fine_go32<Op<float, POT>, FOUR32>(a, s);
+    else fine_go32<Op<float, POT>, false>(a, s);
+}
+// FP32: the one-sided kernels' order of factors (and FP64 slots) where those would run, the coarser tiles'
+// (FP32 slots, four i chunks) from their sizes on
+template <bool POT> static void fine_go_gravity(const FineLaunch &a, hipStream_t s)
+{
+    if (a.prec == P_FP64) fine_go<GravOp<double, POT>, P_FP64, true>(a, s);
+    else if (a.wide) fine_go32<GravOp<float, POT, true>, true>(a, s);
+    else if (a.prec == P_KAHAN) fine_go4<GravOp<float, POT>, P_KAHAN>(a, s);
+    else fine_go4<GravOp<float, POT>, P_FP64ACC>(a, s);
 }
 template <typename T, bool POT> using LjcLinOp = LjcOp<T, POT, LJC>;
 template <typename T, bool POT> using LjcConstOp = LjcOp<T, POT, LJC_CONST>;
@@ -555,10 +572,10 @@ template <typename T, bool POT> using LjcSigOp = LjcOp<T, POT, LJC_SIG>;
 template <bool POT> static void fine_go_force(const FineLaunch &a, hipStream_t s)
 {
     switch (a.law) {
-    case GRAVITY: return fine_go_law<GravOp, POT, true>(a, s);
-    case LJC: return fine_go_law<LjcLinOp, POT, false>(a, s);
-    case LJC_CONST: return fine_go_law<LjcConstOp, POT, false>(a, s);
-    default: return fine_go_law<LjcSigOp, POT, false>(a, s);
+    case GRAVITY: return fine_go_gravity<POT>(a, s);
+    case LJC: return fine_go_law<LjcLinOp, POT>(a, s);
+    case LJC_CONST: return fine_go_law<LjcConstOp, POT>(a, s);
+    default: return fine_go_law<LjcSigOp, POT>(a, s);
     }
 }
 
@@ -585,6 +602,7 @@ static bool fine_valid(const FineLaunch &a)
 {
     if (!fine_supported(a.op, a.law, a.prec) || a.n <= 0 || a.n > kFineMaxN) return false;
     if (a.ich != kFineIch && !(a.ich == kFineIch4 && fine_has4(a.op, a.law, a.prec))) return false;
+    if (a.op == FINE_FORCE && a.law == GRAVITY && a.prec != P_FP64 && !a.wide && a.ich != kFineIch4) return false;
     const int ch = kFineWaves * a.ich;
     if (a.nch != (int)((a.n + kWave - 1) / kWave) || a.nb != (a.nch + ch - 1) / ch) return false;
     const int total = fine_begin(a.nb, a.nch, ch);
