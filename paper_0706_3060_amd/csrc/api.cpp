@@ -1141,6 +1141,8 @@ FineLaunch make_fine(int op, const nbody_law *law, int64_t n, int ich, bool pot,
     a.eps2 = law->kind == NBODY_LAW_GRAVITY ? law->softening * law->softening : 0.0;
     for (int c = 0; c < 4; ++c) a.zeta[c] = law->kind == NBODY_LAW_LJC_SIGMOIDAL ? law->zeta[c] : 0.0;
     a.wide = fine_wide(n, law->precision) ? 1 : 0;
+    // (a piece of 16 quarters adds 256 terms to an i sum: no more than a one-sided tile's FP32 partial)
+    a.wide_i = a.wide && (!is_f32(law->precision) || a.per > 16);
     const FineSlots f = fine_slots(n, ich, a.nwg, op, law->precision);
     a.rec = rec;
     a.jslot = slots;

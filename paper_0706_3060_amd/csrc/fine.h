@@ -39,7 +39,7 @@ struct FineLaunch {
     int ich;                       // i chunks of a wave, 2 or 4
     int nch, nb;                   // chunks and blocks of the n particles
     int per, nwg;                  // quarters per workgroup (>= 4), workgroups
-    int wide;                      // FP32 pair arithmetic: the slots are FP64, not FP32 (FP64: always)
+    int wide, wide_i;              // FP32 pair arithmetic: the j slots and carries, and the i slots, are FP64
     double eps2;
     double zeta[4];
     const void *rec;               // records, padded to whole blocks

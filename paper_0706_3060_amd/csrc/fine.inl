@@ -23,7 +23,9 @@
 // partials folded with compensation).  j sums: a wave's terms of a sweep in the law's type, 128 with
 // two i chunks and 256 with four, and the four waves' sums in FP64.  FP32 chains of at most 256 are what
 // the one-sided kernels add before they fold, and like theirs the slots are FP64 (`wide`) below the
-// coarser tiles' sizes; from there on FP32 as those tiles' are.  Every slot row is written once;
+// coarser tiles' sizes; from there on FP32 as those tiles' are.  The i slots of pieces of at most 16
+// quarters hold no more than such a chain, 256 terms, and are FP32 at every size (8,192 LJC(linear) atoms
+// with energies: 12 MB of FP64 i slots, all stored at the launch's end, cost 3 us of 45).  Every slot row is written once;
 // k_fine_reduce adds a row's j slots, carries and i sums in a fixed order in FP64 with compensation, so
 // results repeat bit for bit.
 #include "allpairs.h"
@@ -455,7 +457,7 @@ void k_fine(FineLaunch a)
         }
         if (!more || over) {
             const int64_t at = ((int64_t)(wg + b) * kRows + w * I * kWave + lane) * NCP;
-            if (sizeof(T) == 8 || a.wide) put_sums<double, NC, NCP>((double *)a.islot + at, acc);
+            if (sizeof(T) == 8 || a.wide_i) put_sums<double, NC, NCP>((double *)a.islot + at, acc);
             else put_sums<float, NC, NCP>((float *)a.islot + at, acc);
             if (!more) return;
             ++b;
@@ -473,7 +475,7 @@ void k_fine(FineLaunch a)
 // few rows and up to a hundred terms a row), each wave adding its own in order, and the waves' sums
 // merged in wave order, all in FP64 with compensation.  The operator's epilogue is separate for each
 // column.
-template <typename T, typename S, int NCP>
+template <typename T, typename SJ, typename SI, int NCP>
 __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
 {
     __shared__ double part[kRedWaves][2][kWave];
@@ -485,9 +487,9 @@ __global__ __launch_bounds__(kRedWaves * kWave) void k_fine_reduce(FineLaunch a)
     const int jc = (int)(blockIdx.x / NCP);                     // 64 (row, column) pairs lie in one chunk
     const int ch = kFineWaves * a.ich, rows = ch * kWave;        // of a block
     const int b = jc / ch, nch = a.nch, per = a.per;
-    const S *__restrict__ jslot = (const S *)a.jslot + t;
-    const S *__restrict__ carry = (const S *)a.carry + (t - (int64_t)jc * kWave * NCP);
-    const S *__restrict__ islot = (const S *)a.islot + (t - (int64_t)b * rows * NCP);
+    const SJ *__restrict__ jslot = (const SJ *)a.jslot + t;
+    const SJ *__restrict__ carry = (const SJ *)a.carry + (t - (int64_t)jc * kWave * NCP);
+    const SI *__restrict__ islot = (const SI *)a.islot + (t - (int64_t)b * rows * NCP);
     NSum v;
     // fine_jslot(k), kRedWaves blocks a time
     int at = fine_jslot(w, a.nb, rows), step = rows * kRedWaves * (2 * (a.nb - w) - kRedWaves - 1) / 2;
@@ -600,7 +602,7 @@ bool fine_has4(int op, int law, int prec)
 // a launch description that does not match the work of n particles is refused, never launched
 static bool fine_valid(const FineLaunch &a)
 {
-    if (!fine_supported(a.op, a.law, a.prec) || a.n <= 0 || a.n > kFineMaxN) return false;
+    if (!fine_supported(a.op, a.law, a.prec) || a.n <= 0 || a.n > kFineMaxN || (a.wide_i && !a.wide)) return false;
     if (a.ich != kFineIch && !(a.ich == kFineIch4 && fine_has4(a.op, a.law, a.prec))) return false;
     if (a.op == FINE_FORCE && a.law == GRAVITY && a.prec != P_FP64 && !a.wide && a.ich != kFineIch4) return false;
     const int ch = kFineWaves * a.ich;
@@ -622,16 +624,21 @@ hipError_t launch_fine(const FineLaunch &a, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int NCP> static void fine_reduce_go(const FineLaunch &a, dim3 grid, dim3 block, hipStream_t s)
+{
+    if (a.wide_i) hipLaunchKernelGGL((k_fine_reduce<float, double, double, NCP>), grid, block, 0, s, a);
+    else if (a.wide) hipLaunchKernelGGL((k_fine_reduce<float, double, float, NCP>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_fine_reduce<float, float, float, NCP>), grid, block, 0, s, a);
+}
+
 hipError_t launch_fine_reduce(const FineLaunch &a, hipStream_t s)
 {
     if (!fine_valid(a)) return hipErrorInvalidValue;
     const int cols = fine_cols(a.op);
     const dim3 grid((unsigned)(a.nch * cols)), block(kRedWaves * kWave);
-    if (a.prec == P_FP64) hipLaunchKernelGGL((k_fine_reduce<double, double, 4>), grid, block, 0, s, a);
-    else if (cols == 4 && a.wide) hipLaunchKernelGGL((k_fine_reduce<float, double, 4>), grid, block, 0, s, a);
-    else if (cols == 4) hipLaunchKernelGGL((k_fine_reduce<float, float, 4>), grid, block, 0, s, a);
-    else if (a.wide) hipLaunchKernelGGL((k_fine_reduce<float, double, 8>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_fine_reduce<float, float, 8>), grid, block, 0, s, a);
+    if (a.prec == P_FP64) hipLaunchKernelGGL((k_fine_reduce<double, double, double, 4>), grid, block, 0, s, a);
+    else if (cols == 4) fine_reduce_go<4>(a, grid, block, s);
+    else fine_reduce_go<8>(a, grid, block, s);
     return hipGetLastError();
 }
 
