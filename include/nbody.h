@@ -227,7 +227,7 @@ typedef struct nbody_exclusions {
  *             (FP32_KAHAN, FP32_FP64ACC) or 262,144 (FP64, forces and leapfrog).
  *             The rule's choice above the row groups: for FP32 up to 32,767
  *             particles (forces and leapfrog of every law, gravity's backward,
- *             LJC(linear)'s from 4,097 to 16,383 atoms, the shared Hermite
+ *             LJC(linear)'s from 2,560 to 16,383 atoms, the shared Hermite
  *             steps), for FP64 everywhere it applies.  From 32,768 to 65,536
  *             particles in FP32 (not the jerk and LJC(linear)'s backward) the
  *             rule reports a shape of j_stage 2, and that shape runs as the fine

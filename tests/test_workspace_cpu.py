@@ -1,4 +1,4 @@
-"""Workspace sizes and a line of the rule (host only): what the fine pair tiles (j_stage 3) add to FP64 forces and leapfrog calls.
+"""Workspace sizes (host only): what the fine pair tiles (j_stage 3) add to FP64 forces and leapfrog calls.
 
 A one-sided call needs the records and up to 64 j parts of 32 bytes a particle.  The fine tiles' slots are
 reused from that space up to 131,072 particles but for the workgroups' own rows (at most 35 MB), and
@@ -26,13 +26,3 @@ def test_fp64_workspace_against_the_j_parts(api, kind, record):
         assert w >= one_sided
         if n > 1 << 18:
             assert w <= one_sided + 1024, n
-
-
-def test_ljc_adjoint_rule_around_4096_atoms():
-    # six FP64 sums a slot: the fine tiles are slower than the one-sided kernel up to 4,096 atoms
-    for prec in (1, 2):
-        law = N.NBodyLaw(1, prec, 1.0, 0.0, 332.0637, 4.0)
-        for n, stage in [(2600, 1), (4096, 1), (4097, 3), (16383, 3), (16384, 2)]:
-            c = N.NBodyConfig()
-            assert N.lib().nbody_get_config(2, n, 1, ctypes.byref(law), ctypes.byref(c)) == 0
-            assert c.j_stage == stage, (prec, n, c.j_stage)
