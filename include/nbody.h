@@ -106,9 +106,9 @@ enum nbody_precision {
 };
 /* A tile partial is a plain FP32 sum: of j_tile terms (256 by the rule) in the
  * one-sided kernels, of at most 128 in the row groups, of 64 for the i side and
- * 128 or 256 (i_per_lane 2 or 4) for the j side in the fine pair tiles.  What
- * follows is the running sum named above, and FP64 across j parts, waves and
- * workgroups.  Where the symmetric tiles (j_stage 2) apply, and in the fine
+ * 128 or 256 (i_per_lane 2 or 4) for the j side in the fine pair tiles (where
+ * an i sum of up to 256 terms may be one).  What follows is the running sum
+ * named above, and FP64 across j parts, waves and workgroups.  Where the symmetric tiles (j_stage 2) apply, and in the fine
  * tiles from 32,768 particles on, a tile's sum for a particle is stored in
  * FP32 between two kernels, under either running sum, and the j side of a
  * symmetric tile is a plain FP32 sum over the tile's rows (256, 1024 or 2048);

@@ -150,20 +150,22 @@ size_t symadj_ljc_partial_bytes(int64_t n)
 // units small enough to fill the chip between the smallest systems and the sizes of the coarser
 // tiles; and, for FP64 pair arithmetic, which has no coarser tiles, up to kFineMaxN (1.2 GB of slots).
 // The rule's lines, per call against the one-sided kernels (us, FP32 + Kahan unless said): at 2,050
-// particles 18-22 against 21-26 for gravity, LJC(linear), the jerk and gravity's adjoint, FP64 22
-// against 23; at 8,192 gravity 29 against 39, LJC(linear) with energies 38 against 52, the jerk 48
-// against 64, gravity's adjoint 37 against 60, FP64 gravity 49 against 86; at 50,001 FP64 gravity 1,158
-// against 1,870.  LJC(linear)'s adjoint, six sums a particle: 28 against 25 at 2,050, 28 against 32 at
-// 3,000, 64 against 91 at 8,192; from 16,384 atoms its 256-record tiles do as well.  From 32,768 FP32
-// particles the coarser tiles do as well (within 3 % at 50,001) with fewer slots.
+// particles 17-21 against 17-25 for gravity, LJC(linear), the jerk and gravity's adjoint, FP64 gravity 18
+// against 20; at 8,192 gravity 31 against 34, LJC(linear) with energies 39 against 49, the jerk 50
+// against 71, gravity's adjoint 38 against 55, FP64 gravity 50 against 58; at 50,001 FP64 gravity 1,075
+// against 1,870.  LJC(linear)'s adjoint, six sums a particle: 27 against 27 at 2,050, 28 against 31 at
+// 3,000, 34 against 32 at 4,096, 34 against 42 at 4,500, 65 against 82 at 8,192; from 16,384 atoms the rule
+// keeps its 256-record tiles (at 20,000 they take 362 against 273, at 33,000 731 against 696).  From 32,768
+// FP32 particles the rule names the coarser tiles, which need fewer slots (kFineForSym).
 constexpr int kFineStage = 3;
 constexpr int64_t kFineMinN = 2048;
 constexpr int64_t kFineMaxN32 = int64_t(1) << 17;
 constexpr int64_t kFineAdjLjcMinN = 2560;
 // Four i chunks a wave halve the j sums' moves a pair, which two make up for in balance below (FP64
-// gravity with potentials: 52 us with two chunks against 55 at 8,192 particles, 163 against 162 at
-// 18,000, 425 against 397 at 30,011, 1,147 against 1,075 at 50,001, 7,973 against 7,273 at 131,072; FP32
-// without them 52 against 55 at 12,000, 94 against 91 at 18,000, 213 against 201 at 30,011).
+// gravity with potentials: 50 us with two chunks against 52 at 8,192 particles, 139 against 138 at
+// 16,000, 210 against 205 at 20,000, 425 against 397 at 30,011, 1,147 against 1,075 at 50,001; FP32
+// without them 49 against 52 at 12,000, 74 against 76 at 16,000, 110 against 107 at 20,000, 219 against
+// 208 at 30,011).
 constexpr int64_t kFineMin4 = 20480;
 // From this size (padded to 64) only four chunks, where they are built: two take twice the slots and are
 // slower, and FP32 gravity has them with FP64 slots only (fine_wide).
@@ -190,10 +192,10 @@ int64_t fine_max_n(int api, int law, int prec)
 }
 // Row groups (rows.inl): small systems' forces and leapfrog steps in one launch each, reported as
 // j_stage 3 with the workgroup of 1,024 threads.  The rule's line, per call against the fine tiles
-// (us): at 4,096 particles FP32 gravity 14 against 20, LJC(linear) 18 against 22, LJC(sigmoidal) 25
-// against 27, FP64 gravity 19 against 23; at 5,000 FP32 gravity 23 against 20.  One-sided FP64 LJC
-// pairs cost more: LJC(linear) 22 against 22 at 3,000, LJC(sigmoidal) 26 against 29 at 2,050 and 34
-// against 29 at 3,000.  (Three launches of the one-sided kernels: 20-21 at any size below 2,000.)
+// (us): at 4,096 particles FP32 gravity 12 against 18 (13 against 19 with potentials), LJC(linear) 17
+// against 22, FP64 gravity 18 against 22.  One-sided FP64 LJC pairs cost more: LJC(linear) 20 against
+// 21 at 3,000 and 26 against 25 at 4,096, LJC(sigmoidal) 26 against 29 at 2,050 and 34 against 29 at
+// 3,000.  (Three launches of the one-sided kernels: 20-21 at any size below 2,000.)
 constexpr int kRowsBlock = 1024;
 int64_t rows_rule_n(int law, int prec)
 {
