@@ -177,7 +177,7 @@ def main():
 
     # issue-rate ceiling of the timed kernel's instruction sequence, measured on this GPU,
     # per interaction-wave (64 interactions of 20 flops against 64 flops per SIMD-cycle at
-    # peak; 157.3 TFLOP/s is that at 2.4 GHz).  Symmetric pair tiles (j_stage 2): one
+    # peak; 157.3 TFLOP/s is that at 2.4 GHz).  Symmetric and fine pair tiles (j_stage 2, 3): one
     # unordered pair-wave is 18 ordinary FP32 VALU instructions, one v_rsq_f32 and half a
     # DPP move (the potential's j sum; the force sums move through the LDS crossbar, off
     # the VALU) for two interactions; one-sided kernels: 13 ordinary instructions and one
@@ -185,7 +185,7 @@ def main():
     # is not visible here: clock_for_kernel_ghz is the clock at which the measured launch
     # time equals the modelled cycles.
     rates = nb.probe_issue_rates(dev)
-    if cfg_used["j_stage"] == 2:
+    if cfg_used["j_stage"] == 2 or (cfg_used["j_stage"] == 3 and cfg_used["block"] == 256):
         inter_cycles = (18 * rates["fma_cycles"] + rates["rsq_cycles"] + 0.5 * rates["dpp_mov_cycles"]) / 2.0
         model = "symmetric: (18 VALU + 1 rsq + 0.5 DPP move) per unordered pair-wave, two interactions"
     else:
@@ -297,6 +297,8 @@ def timed_kernel(n, cfg):
     the symmetric pair tiles (j_stage 2; one 512-thread workgroup per tile of the block
     grid's upper triangle, the count padded to a multiple of the 8 XCDs) or the one-sided
     forces kernel."""
+    if cfg["j_stage"] == 3:
+        raise SystemExit("no traffic record of the small systems' kernels (j_stage 3)")
     if cfg["j_stage"] == 2:
         rec = cfg["j_tile"]
         nblk = -(-n // rec)

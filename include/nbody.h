@@ -108,11 +108,11 @@ enum nbody_precision {
  * one-sided kernels, of at most 128 in the row groups, of 64 for the i side and
  * 128 or 256 (i_per_lane 2 or 4) for the j side in the fine pair tiles (where
  * an i sum of up to 256 terms may be one).  What follows is the running sum
- * named above, and FP64 across j parts, waves and workgroups.  Where the symmetric tiles (j_stage 2) apply, and in the fine
- * tiles from 32,768 particles on, a tile's sum for a particle is stored in
- * FP32 between two kernels, under either running sum, and the j side of a
- * symmetric tile is a plain FP32 sum over the tile's rows (256, 1024 or 2048);
- * these are then added in FP64.
+ * named above, and FP64 across j parts, waves and workgroups.  In the symmetric
+ * tiles (j_stage 2), and in the fine tiles from 32,768 particles on, a tile's
+ * sum for a particle is stored in FP32 between two kernels, under either
+ * running sum, and the j side of a symmetric tile is a plain FP32 sum over the
+ * tile's rows (256, 1024 or 2048); these are then added in FP64.
  * Range in FP32: for gravity's forces and jerk the one-sided kernels, the row
  * groups and the fine tiles below 32,768 particles form m / s^3 as (m / s) /
  * s^2; the other tiles form m s^-3, and the adjoints s^-3 everywhere, for
@@ -221,9 +221,10 @@ typedef struct nbody_exclusions {
  *             particles (not FP32_PLAIN); the rule's choice there (FP64 LJC: up
  *             to 3,072 atoms, 2,304 with the sigmoidal dielectric).  Otherwise
  *             fine pair tiles (block 256, i_per_lane 2 or 4, j_tile 256 times
- *             that; 4 for the forces in FP64 and of gravity in FP32): each
- *             unordered pair of a whole system once, in quarter sweeps shared out
- *             equally over the workgroups, for up to 131,072 particles
+ *             that; 4 for the forces in FP64 and of gravity in FP32, where 2
+ *             reads as 4 above 32,704 particles): each unordered pair
+ *             of a whole system once, in quarter sweeps shared out equally over
+ *             the workgroups, for up to 131,072 particles
  *             (FP32_KAHAN, FP32_FP64ACC) or 262,144 (FP64, forces and leapfrog).
  *             The rule's choice above the row groups: for FP32 up to 32,767
  *             particles (forces and leapfrog of every law, gravity's backward,
@@ -366,14 +367,15 @@ int nbody_forces_batched(const int64_t *offsets, int64_t n_systems, const double
  *              beyond); atoms whose type is outside [0, n_types) are not
  *              counted.
  * Swapping k and j negates both d and m_k g_j - m_j g_k, so gravity's pair
- * term for j is minus its term for k: with FP32 pair arithmetic and 65,536
- * to 2,097,152 particles the rule evaluates each unordered pair once
- * (symmetric pair tiles, as the forward's).  LJC(linear)'s position terms
- * of the two atoms are likewise opposite and its charge, sigma and epsilon
- * terms share one scalar: with FP32 pair arithmetic, no exclusion lists and
- * 16,384 to 262,144 atoms the rule evaluates each unordered pair once too
- * (j_stage 2: the batched backward's tiles of 256 x 256 records over the one
- * system; any size up to 262,144 when forced).
+ * term for j is minus its term for k: with FP32 pair arithmetic and 2,048 to
+ * 2,097,152 particles the rule evaluates each unordered pair once (fine pair
+ * tiles, and symmetric pair tiles above 65,536, as the forward's).
+ * LJC(linear)'s position terms of the two atoms are likewise opposite and its
+ * charge, sigma and epsilon terms share one scalar: with FP32 pair arithmetic,
+ * no exclusion lists and 2,560 to 262,144 atoms the rule evaluates each
+ * unordered pair once too (fine pair tiles, and from 16,384 atoms j_stage 2:
+ * the batched backward's tiles of 256 x 256 records over the one system; any
+ * size up to 262,144 when forced).
  * Workspace: nbody_workspace_bytes(NBODY_API_BACKWARD, n, 1, law); for
  * LJC(linear) with FP32 and n <= 262,144 it covers 32 bytes of slot
  * partials per atom and 256-record block (8 GiB at 262,144).
