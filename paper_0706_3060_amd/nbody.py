@@ -145,11 +145,15 @@ def _params(params, n, law, device):
 _ws = {}
 
 
-def workspace(api, n_total, n_systems, law: Law, device) -> torch.Tensor:
-    """A cached uint8 device buffer at least nbody_workspace_bytes() long (per device and stream)."""
+def workspace(api, n_total, n_systems, law: Law, device, tiles: bool = True) -> torch.Tensor:
+    """A cached uint8 device buffer at least nbody_workspace_bytes() long (per device and stream);
+    without `tiles`, the forces of row subsets and exclusion lists, as long as those need."""
     nbytes = N.lib().nbody_workspace_bytes(api, int(n_total), int(n_systems), ctypes.byref(law.c()))
     if nbytes == 0 and n_total > 0:
         raise ValueError("invalid workspace request")
+    if not tiles:
+        record = (4 if law.kind == GRAVITY else 8) * (8 if law.precision == FP64 else 4)
+        nbytes = min(nbytes, -(-max(int(n_total), 1) // 64) * 64 * (2048 + record) + 512)
     dev = torch.device(device)
     key = (dev.index, _raw_stream(dev))
     buf = _ws.get(key)
@@ -175,7 +179,7 @@ def forces(pos, params, law: Law, potential: bool = True, out=None, exclusions: 
     par = _params(params, n, law, pos.device)
     f = out if out is not None else torch.empty((n, 3), dtype=torch.float64, device=pos.device)
     p = torch.empty(n, dtype=torch.float64, device=pos.device) if potential else None
-    ws = workspace(API_FORCES, n, 1, law, pos.device)
+    ws = workspace(API_FORCES, n, 1, law, pos.device, tiles=exclusions is None)
     if exclusions is None:
         N.check(N.lib().nbody_forces(_ptr(pos), _ptr(par), n, ctypes.byref(law.c()), _ptr(f), _ptr(p),
                                      _ptr(ws), ws.numel(), _stream(pos.device)))
@@ -218,7 +222,7 @@ def forces_subset(pos, params, ilist, law: Law, potential: bool = True):
         raise ValueError("ilist indices must lie in [0, %d)" % n)
     f = torch.empty((ni, 3), dtype=torch.float64, device=pos.device)
     p = torch.empty(ni, dtype=torch.float64, device=pos.device) if potential else None
-    ws = workspace(API_FORCES, max(n, ni), 1, law, pos.device)
+    ws = workspace(API_FORCES, max(n, ni), 1, law, pos.device, tiles=False)
     N.check(N.lib().nbody_forces_subset(_ptr(pos), _ptr(par), n, _ptr(il), ni,
                                         ctypes.byref(law.c()), _ptr(f), _ptr(p), _ptr(ws),
                                         ws.numel(), _stream(pos.device)))

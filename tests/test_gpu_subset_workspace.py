@@ -56,3 +56,27 @@ def test_subset_and_exclusions_in_a_small_workspace(prec, n):
     N.check(lib.nbody_forces_excl(ptr(Y), ptr(P), n, ctypes.byref(e), ctypes.byref(law.c()), ptr(f), ptr(p), ptr(ws),
                                   ws.numel(), stream))
     assert torch.equal(f, ref) and torch.equal(p, refp)
+
+
+@pytest.mark.parametrize("law,prec", [("gravity", "fp64"), ("ljc", "fp64"), ("gravity", "fp32_kahan"),
+                                      ("ljc", "fp32_fp64acc")])
+@pytest.mark.parametrize("n,ni", [(1, 3), (63, 5), (1000, 1000), (4097, 64), (40001, 50000), (140001, 200)])
+def test_the_binding_brings_no_more(law, prec, n, ni):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0706_3060_amd import nbody as nb
+    g = np.random.default_rng(n)
+    side = int(np.ceil(n ** (1 / 3)))
+    pos = dev(3.2 * np.stack(np.unravel_index(np.arange(n), (side,) * 3), axis=1) + g.uniform(-0.3, 0.3, (n, 3)))
+    lw = nb.gravity(prec, softening=0.1) if law == "gravity" else nb.ljc_linear(prec)
+    par = dev(g.uniform(0.5, 1.0, n) if law == "gravity" else
+              np.stack([g.uniform(-0.5, 0.5, n), np.full(n, 3.2), np.full(n, 0.1)], axis=1))
+    rows = dev(g.integers(0, n, ni), torch.int64)
+    nb.clear_workspace_cache()
+    f, u = nb.forces_subset(pos, par, rows, lw)
+    size = max(b.numel() for b in nb._ws.values())
+    m = -(-max(n, ni) // 64) * 64
+    assert size <= m * (2048 + (4 if law == "gravity" else 8) * (8 if prec == "fp64" else 4)) + 512
+    nb.forces(pos, par, lw)                       # a larger buffer: the same sums
+    f2, u2 = nb.forces_subset(pos, par, rows, lw)
+    assert torch.equal(f, f2) and torch.equal(u, u2)
